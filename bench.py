@@ -197,10 +197,12 @@ def trace_summary(d: str, warmup: int, steps: int) -> dict:
 
 def attention_kernel_name(line: dict) -> str:
     """The attention kernel a bench line's launch ran: by dtype and
-    workgroup shape (config.row_group, config.packed)."""
+    workgroup shape (config.balanced, config.row_group, config.packed)."""
+    cfg = line.get("config", {})
+    if cfg.get("balanced"):
+        return "cascade_balanced_kernel"
     if line.get("dtype") != "bf16":
         return "cascade_attention_kernel"
-    cfg = line.get("config", {})
     if cfg.get("packed"):
         return "cascade_bf16_packed_kernel"
     if cfg.get("row_group") == 384:
@@ -419,6 +421,8 @@ def main():
     ws_bytes = d2sd.cascade_workspace_size(a)
     kv_split = d2sd.cascade_kv_split(a)
     row_group, packed = d2sd.cascade_shape(a)
+    # the even division keeps a count per stream beside the partial states, the fixed splits do not
+    balanced = ws_bytes % (total * spec.hq * (spec.head_dim * (2 if spec.dtype == "bf16" else 4) + 8)) != 0
     n_splits = -(-max_ctx // kv_split) if max_ctx > 0 else 1
     ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
     acc = d2sd.accept_path(B, d_ip, total, tree["parent"], tree["depth"], tree["path_id"], d_draft, d_argmax)
@@ -455,7 +459,7 @@ def main():
         # the keys read by --record-traffic: dtype, config, requested_kv_split, roofline.splits
         print(json.dumps({"profile_stage": args.profile_stage, "dtype": spec.dtype, "calls": len(kern),
                           "config": {"workload": spec.name, "kv_split": kv_split, "row_group": row_group,
-                                     "packed": packed, "tree": args.tree},
+                                     "packed": packed, "balanced": balanced, "tree": args.tree},
                           "requested_kv_split": args.kv_split, "roofline": {"splits": splits},
                           "kernel_ms": round(k_ms, 4), "merge_ms": round(float(np.mean(merge)), 4),
                           "algorithmic_flop_per_call": flops, "tflops": round(flops / (k_ms / 1e3) / 1e12, 3)}),
@@ -606,7 +610,7 @@ def main():
         "config": {"workload": spec.name, "batch": layout.batch,
                    "ctx_len": [int(ctx.min()), int(ctx.max())], "q_heads": Hq, "kv_heads": Hkv,
                    "head_dim": D, "block": B, "branches": spec.K, "tree_nodes": total,
-                   "page_size": spec.page_size, "kv_split": kv_split, "row_group": row_group, "packed": packed,
+                   "page_size": spec.page_size, "kv_split": kv_split, "row_group": row_group, "packed": packed, "balanced": balanced,
                    "tree": args.tree},
         "roofline": roof,
         "roofline_note": ("mfma-bound: the workload's algorithmic flops at the bf16 dense peak take longer "

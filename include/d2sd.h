@@ -285,6 +285,9 @@ d2sd_status d2sd_cascade_workspace_size(const d2sd_attn_args* args, size_t* byte
 /*
  * Host. The context split length (tokens, multiple of 64) the attention call
  * will use for `args` (args->kv_split if nonzero, else the automatic choice).
+ * Where the automatic plan divides the batch's keys evenly over the CUs (see
+ * d2sd_cascade_verify_attention), streams are cut anywhere and this is the
+ * nominal length of the fixed splits it replaces.
  */
 d2sd_status d2sd_cascade_kv_split(const d2sd_attn_args* args, int* kv_split);
 
@@ -292,7 +295,8 @@ d2sd_status d2sd_cascade_kv_split(const d2sd_attn_args* args, int* kv_split);
  * Host. The query rows per workgroup (128 or 384) the attention call will use
  * for `args` (args->row_group if nonzero, else the automatic choice), and in
  * *packed (nullable) 1 when the 384-row workgroups run over the sequence of
- * all streams' tiles (args->packed), else 0.
+ * all streams' tiles (args->packed), else 0. 128 also stands for the even
+ * division (row groups of up to 384 rows there).
  */
 d2sd_status d2sd_cascade_row_group(const d2sd_attn_args* args, int* rows, int* packed);
 
@@ -305,7 +309,10 @@ d2sd_status d2sd_cascade_row_group(const d2sd_attn_args* args, int* rows, int* p
  * (context split, workgroup) and reused by all rows the workgroup holds of
  * that stream, i.e. by all G query heads of their tree nodes. The
  * workgroups of one stream run as neighbours on one XCD, so that later
- * readers of a slab can hit its L2.
+ * readers of a slab can hit its L2. With kv_split = 0 and row_group = 0 the
+ * automatic plan may instead give every CU an equal share of the batch's key
+ * tiles, computed on the device from node_indptr and ctx_len (fp32, and bf16
+ * grids that fixed splits fill badly); up to 384 rows then share a slab.
  * ws: device workspace of ws_bytes >= d2sd_cascade_workspace_size(args) (may
  * be NULL when that size is 0). Concurrent calls must not share a workspace.
  */
@@ -321,8 +328,8 @@ d2sd_status d2sd_cascade_verify_attention(const d2sd_attn_args* args, void* ws, 
  * every GPU the library runs on until the process ends. With an explicit
  * kv_split whose partial states exceed 64 MiB it returns
  * D2SD_ERR_WORKSPACE_TOO_SMALL; with the automatic split (kv_split = 0) it
- * takes the automatic plan, or, when that does not fit, the fewest-split
- * longer splits that do (the results then differ from the workspace entry
+ * takes the automatic plan, or, when that does not fit, fewer and longer
+ * splits that do (the results then differ from the workspace entry
  * point's by summation order only), and returns D2SD_ERR_WORKSPACE_TOO_SMALL
  * if even ceil(max_ctx_len / 32768) splits do not fit. The scratch holds
  * nothing that must start at zero; every call on one GPU shares it and

@@ -259,6 +259,51 @@ double packed_time(long long tiles1, int s) {
   return rounds_time(wgs, kNumCUs, 1) / s;
 }
 
+// Grid of the balanced shape (one workgroup per CU), or 0 where its 32-bit
+// cost positions or its LDS scan would not hold the batch.
+int balanced_workgroups(const d2sd_attn_args* a, int G) {
+  if (a->batch > d2sd::kBalancedMaxBatch || (long long)a->max_nodes * a->num_qo_heads >= (1ll << 21)) return 0;
+  const long long key_tiles = ((long long)a->max_ctx_len + 31) / 32 + ((long long)a->max_nodes + 31) / 32 + 1;
+  const long long query_tiles = ((long long)a->max_nodes * G + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile;
+  const long long groups = (query_tiles + d2sd::kBalWaves - 1) / d2sd::kBalWaves;
+  const long long stream = key_tiles * d2sd::kBalMaxCost + d2sd::kBalOverheadBf16;
+  if (stream * kNumCUs > (1ll << 30)) return 0;
+  if (stream * groups * a->num_kv_heads > (1ll << 30) / a->batch) return 0;
+  return d2sd::kBalWorkgroups;
+}
+
+// Where the even division beats the fixed splits (attention with its merge, us,
+// fixed splits first; 32/8 heads unless said):
+//  - fp32: everywhere a context has more than one split's minimum (4 requests
+//    of 300-3000 tokens: 218 -> 94; 16 of 4000-8000: 1869 -> 762; 64 of
+//    500-1000: 883 -> 442); at a single split's length they are level.
+//  - bf16, grids that do not fill the chip with one split: from 1024 tokens
+//    on (8 requests of 1k-8k: 90 -> 69; 1 of 32k: 74 -> 50; 1 of 1000:
+//    24 -> 23). Below, the second launch costs more than the division gives
+//    (4 of 600-800: 25 -> 28; 16 of 300-500: 23 -> 38).
+//  - bf16, larger grids: with five to eight query tiles per stream, where a
+//    384-row workgroup idles a third of its waves and the four-wave shape
+//    reads the context twice (32 requests of 4k-16k: 485 -> 404; 64 of 16k:
+//    1176 -> 1129). With fewer tiles the four-wave shape is as fast (64 of
+//    8000, 2-3 tiles: 391 -> 398), with more the 384-row shapes are faster
+//    (32 of 16k, 9-11 tiles: 837 -> 857; 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms).
+bool balanced_pays(const d2sd_attn_args* a, int G, bool large_grid) {
+  if (a->dtype == D2SD_F32) return a->max_ctx_len > kMinSplitF32;
+  if (a->max_ctx_len < 1000) return false;
+  const long long tiles = ((long long)a->max_nodes * G + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile;
+  return !large_grid || (tiles > 4 && tiles <= 8);
+}
+
+// Most pieces a stream of the balanced shape is cut into: four times an equal
+// share of the workgroups (contexts up to four times the mean are divided
+// evenly, longer ones less finely), and no more than its key tiles.
+int balanced_pieces(const d2sd_attn_args* a) {
+  const int even = (kNumCUs + a->num_kv_heads - 1) / a->num_kv_heads;      // one request
+  const int wanted = (4 * kNumCUs + a->num_kv_heads * a->batch - 1) / (a->num_kv_heads * a->batch);
+  const int key_tiles = (a->max_ctx_len + 31) / 32 + (a->max_nodes + 31) / 32;
+  return max(2, min(min(even, wanted) + 1, key_tiles));
+}
+
 struct Shape {
   int waves;
   bool packed;
@@ -278,12 +323,15 @@ constexpr double kPackMargin = 0.97;
 //    The packed 12-wave shape fills every wave (workgroups over the sequence
 //    of all streams' tiles) and is counted by its tiles; it is taken only
 //    when it beats the one-stream 12-wave shape by kPackMargin.
-//  - Smaller grids take 4-wave groups and about two rounds of work items.
+//  - Smaller grids take 4-wave groups and about two rounds of work items, or
+//    the balanced shape where balanced_pays says so (its plan keeps the split
+//    length of the fixed splits as a nominal value: d2sd_cascade_kv_split).
 // No split is shorter than the dtype's minimum (the partial state of a split
 // costs as many bytes as ~M/2 keys of K/V, M = rows sharing it; fp32 splits
 // are compute-bound and can be shorter) or longer than the staged page list
 // allows. An explicit kv_split, row_group or packed fixes that choice.
 void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
+  plan->workgroups = 0;
   const bool bf16 = a->dtype == D2SD_BF16;
   const int ctx = a->max_ctx_len;
   const int min_split = bf16 ? kMinSplit : kMinSplitF32;
@@ -341,6 +389,9 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
     const int s = (int)((2 * R4 + g4 - 1) / g4);
     sh.splits = max(s_lo, min(s, s_hi));
   }
+  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, G, g4 * s_lo >= R4))
+    plan->workgroups = balanced_workgroups(a, G);
+  if (plan->workgroups > 0) sh = Shape{d2sd::kBf16Waves, false, sh.splits};
   plan->waves = sh.waves;
   plan->packed = sh.packed;
   plan->tiles = 0;   // the packed shape's tile count is set by make_plan from the resolved split count
@@ -354,6 +405,17 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
   }
 }
 
+// Partial states of one split: per row the normalised output in the input
+// dtype, then m and l in fp32.
+size_t split_bytes(const d2sd_attn_args* a) {
+  const size_t rows = (size_t)a->total_nodes * a->num_qo_heads;
+  return rows * (a->head_dim * (a->dtype == D2SD_BF16 ? 2 : 4) + 2 * sizeof(float));
+}
+// Balanced shape: the number of pieces of every stream.
+size_t piece_count_bytes(const d2sd_attn_args* a, const d2sd::AttnPlan& plan) {
+  return plan.workgroups > 0 ? (size_t)a->batch * a->num_kv_heads * plan.n_rg_max * sizeof(int) : 0;
+}
+
 d2sd_status make_plan(const d2sd_attn_args* a, d2sd::AttnPlan* plan) {
   plan->G = a->num_qo_heads / a->num_kv_heads;
   choose_shape(a, plan->G, plan);
@@ -365,21 +427,20 @@ d2sd_status make_plan(const d2sd_attn_args* a, d2sd::AttnPlan* plan) {
     plan->tiles = tiles1 * plan->n_ch_max;
     if (plan->tiles > (1ll << 30)) return fail(D2SD_ERR_UNSUPPORTED, "too many query tiles (%lld)", plan->tiles);
   }
+  if (plan->workgroups > 0) plan->n_ch_max = balanced_pieces(a);
+  plan->merge_groups = (plan->workgroups > 0 ? plan->workgroups >= 16ll * a->num_kv_heads * a->batch : plan->n_ch_max >= 4) ? 4 : 1;
   const long long max_rows = (long long)a->max_nodes * plan->G;
-  const int rows_per_group = plan->waves * d2sd::kRowsPerTile;
+  const int rows_per_group = (plan->workgroups > 0 ? d2sd::kBalWaves : plan->waves) * d2sd::kRowsPerTile;
   plan->n_rg_max = (int)max(1ll, (max_rows + rows_per_group - 1) / rows_per_group);
   plan->items = (long long)a->batch * a->num_kv_heads * plan->n_ch_max * plan->n_rg_max;
   if (plan->items > (1ll << 30)) return fail(D2SD_ERR_UNSUPPORTED, "too many work items (%lld)", plan->items);
   if (plan->n_ch_max > 1 &&
       (long long)a->batch *
-              d2sd::merge_chunks_per_request(a->max_nodes, a->num_qo_heads, d2sd::merge_groups(plan->n_ch_max)) >
+              d2sd::merge_chunks_per_request(a->max_nodes, a->num_qo_heads, plan->merge_groups) >
           (1ll << 30))
     return fail(D2SD_ERR_UNSUPPORTED, "too many split-merge workgroups (batch %d, max_nodes %d)", a->batch,
                 a->max_nodes);
-  const size_t rows = (size_t)a->total_nodes * a->num_qo_heads;
-  // per split and row: the normalised output in the input dtype, then m and l in fp32
-  const size_t o_elem = a->dtype == D2SD_BF16 ? 2 : 4;
-  plan->ws_bytes = plan->n_ch_max > 1 ? (size_t)plan->n_ch_max * rows * (a->head_dim * o_elem + 2 * sizeof(float)) : 0;
+  plan->ws_bytes = plan->n_ch_max > 1 ? plan->n_ch_max * split_bytes(a) + piece_count_bytes(a, *plan) : 0;
   plan->scale = a->sm_scale > 0.0f ? a->sm_scale : 1.0f / sqrtf((float)a->head_dim);
   return D2SD_OK;
 }
@@ -577,6 +638,15 @@ d2sd_status d2sd_cascade_verify_attention_noalloc(const d2sd_attn_args* args, hi
   if (s) return s;
   d2sd::AttnPlan plan;
   if ((s = make_plan(args, &plan))) return s;
+  if (plan.workgroups > 0 && plan.ws_bytes > d2sd::kScratchBytes) {
+    // the same division with fewer, longer pieces per stream
+    const size_t counts = piece_count_bytes(args, plan);
+    const size_t pieces = counts < d2sd::kScratchBytes ? (d2sd::kScratchBytes - counts) / split_bytes(args) : 0;
+    if (pieces >= 2) {
+      plan.n_ch_max = (int)pieces;
+      plan.ws_bytes = pieces * split_bytes(args) + counts;
+    }
+  }
   if (plan.ws_bytes > d2sd::kScratchBytes) {
     if (args->kv_split > 0)
       return fail(D2SD_ERR_WORKSPACE_TOO_SMALL,

@@ -36,37 +36,11 @@
 
 #include <mutex>
 
-#include "common.h"
+#include "attention_device.h"
 
 namespace d2sd {
 
 namespace {
-
-constexpr int kD = 128;
-constexpr int kThreads = 256;
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-
-struct Params {
-  const void* q;
-  const void* k_cache;
-  const void* v_cache;
-  const int* page_table;
-  const int* ctx_len;
-  const void* k_tree;
-  const void* v_tree;
-  const int* node_indptr;
-  const uint32_t* anc_mask;
-  void* out;
-  float* lse;
-  void* ws_o;   // [n_ch_max, total_rows, D] split outputs normalised by their row sum, in the input dtype
-  float* ws_m;  // [n_ch_max, total_rows]
-  float* ws_l;  // [n_ch_max, total_rows]
-  int batch, hq, hkv, G, stage;
-  int total_nodes, max_nodes, max_ctx, num_pages, max_pages, mask_words;
-  int split, n_ch_max, n_rg_max, items;
-  float c2;  // sm_scale * log2(e)
-};
 
 // Tiling of the generic kernel (instantiated for fp32; bf16 has its own kernel).
 template <typename T>
@@ -81,19 +55,6 @@ struct Tile<float> {
   static constexpr int K_ELEMS = KT * KS;
   static constexpr int V_ELEMS = KT * VS;
 };
-
-__device__ __forceinline__ f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x16 mfma(float a, float b, const f32x16& c) {
-  return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ uint4 zero4() { return make_uint4(0u, 0u, 0u, 0u); }
-
-// s_waitcnt vmcnt(0): wait for every outstanding vector-memory access of the
-// wave (gfx9 encoding: vmcnt 0, expcnt and lgkmcnt left at their maxima).
-__device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
 // Pointer to the first element of key `kabs` of request b / KV head h, or null
 // when the key lies outside [0, key_end). Context keys go through the page
@@ -208,18 +169,6 @@ template <>
 struct Stage<float> {
   using type = StageF32;
 };
-
-template <typename T>
-__device__ __forceinline__ void store_out(T* dst, const float* v4);
-template <>
-__device__ __forceinline__ void store_out<__bf16>(__bf16* dst, const float* v) {
-  __bf16 h[4] = {(__bf16)v[0], (__bf16)v[1], (__bf16)v[2], (__bf16)v[3]};
-  *reinterpret_cast<uint2*>(dst) = *reinterpret_cast<const uint2*>(h);
-}
-template <>
-__device__ __forceinline__ void store_out<float>(float* dst, const float* v) {
-  *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
-}
 
 // kNode: the non-cascade baseline, one workgroup per (request, node, KV
 // head) streaming the whole context for that node's query heads.
@@ -483,47 +432,6 @@ struct Shape {
 };
 }  // namespace bf
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint4 lds_b128(const char* base, int off) {
-  return *reinterpret_cast<const uint4*>(base + off);
-}
-__device__ __forceinline__ s16x4 lds_tr16(const char* base, int off) {
-  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(base + off));
-}
-// LDS DMA copies are issued as inline asm so that the compiler does not
-// track them: its own tracking cannot tell ring stages apart and would make
-// every later LDS read wait for all copies in flight (vmcnt(0)). The kernel
-// orders copies and reads itself (sync_keep); untracked loads can only
-// lengthen the compiler's own vmcnt waits, never shorten them. The s_nop
-// covers the M0-write to LDS-DMA hazard. Each lane's 16 bytes land at
-// M0 + 16 * lane.
-__device__ __forceinline__ uint32_t lds_addr(const char* p) {
-  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)p;
-}
-__device__ __forceinline__ void dma16(const void* src, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(src), "s"(lds)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma16s(const char* base, uint32_t lane_off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(lane_off), "s"(base), "s"(lds)
-               : "memory", "m0");
-}
-
-// s_waitcnt vmcnt(n) lgkmcnt(0) then s_barrier; the asm statement is also a
-// compiler memory barrier. Waves keep up to n of their own LDS DMAs in flight.
-template <int N>
-__device__ __forceinline__ void sync_keep() {
-  static_assert(N >= 0 && N < 64, "vmcnt field");
-  // gfx9 s_waitcnt: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
-  __builtin_amdgcn_s_waitcnt((N & 15) | 0x0070 | ((N >> 4) << 14));
-  asm volatile("s_barrier" ::: "memory");
-}
 struct TileSrc {
   bool tree;
   int key0;
@@ -666,11 +574,6 @@ __device__ __forceinline__ void pv_tile(const char* sV, const ReadLane& rl, cons
       o[dt] = mfma(__builtin_bit_cast(bf16x8, a8), pf[ks], o[dt]);
     }
   }
-}
-
-__device__ __forceinline__ float xhalf_max(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 // Mask keys of a partial or tree tile: slot i of block kb is key
@@ -1357,33 +1260,60 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
   const int chunk = blockIdx.x % chunks;
   const int node_base = clampi(p.node_indptr[b], 0, p.total_nodes);
   const int Nb = clampi(p.node_indptr[b + 1] - node_base, 0, min(p.max_nodes, p.total_nodes - node_base));
-  const int Cb = clampi(p.ctx_len[b], 0, p.max_ctx);
-  const int n_ch_b = max(1, ceil_div(Cb, p.split));
   const int rl = threadIdx.x / (16 * GROUPS);            // row within the workgroup
   const int g = (threadIdx.x / 16) % GROUPS;             // split group
   const int d0 = (threadIdx.x & 15) * 8;
   const int r = chunk * ROWS + rl;                        // row within the request
-  const bool live = n_ch_b > 1 && r < Nb * p.hq;
+  // splits of the row: those of the request's context, or, in the balanced
+  // shape, the pieces of the row's stream (quotients of numbers below 2^21 by
+  // float reciprocals: integer divisions were most of the kernel's time)
+  int n_splits = 0;
+  if (!p.ws_pieces) {
+    n_splits = ceil_div(clampi(p.ctx_len[b], 0, p.max_ctx), p.split);
+  } else if (r < Nb * p.hq) {
+    const int node = (int)(((float)r + 0.5f) * p.inv_hq);
+    const int hh = r - node * p.hq;
+    const int h = (int)(((float)hh + 0.5f) * p.inv_G);
+    const int tile = (node * p.G + hh - h * p.G) / kRowsPerTile;
+    const int tiles = ceil_div(Nb * p.G, kRowsPerTile);
+    int rgi = 0;
+    if (tiles > kBalWaves) rgi = tile / ceil_div(tiles, ceil_div(tiles, kBalWaves));
+    n_splits = p.ws_pieces[((size_t)b * p.hkv + h) * p.n_rg_max + rgi];
+  }
+  const bool live = n_splits > 1 && r < Nb * p.hq;
   const int row = node_base * p.hq + r;
   const size_t stride = (size_t)p.total_nodes * p.hq;
-  float M = -INFINITY, L = 0.0f;
+  // A group folds BATCH of its splits at a time: their loads go out together,
+  // the last ones repeated with weight 0. The reference starts below every
+  // score but finite, so that an empty split (m = -inf) weighs 0.
+  constexpr int BATCH = 4;
+  float M = -3.0e38f, L = 0.0f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (live) {
-#pragma unroll 4
-    for (int s = g; s < n_ch_b; s += GROUPS) {
-      const size_t pr = s * stride + row;
-      const float ms = p.ws_m[pr];
-      const float ls = p.ws_l[pr];
-      float v[8];
-      load_partial8(static_cast<const T*>(p.ws_o) + pr * kD + d0, v);
-      const float Mn = fmaxf(M, ms);
-      if (Mn == -INFINITY) continue;                        // no keys so far
-      const float a = __builtin_amdgcn_exp2f(M - Mn);       // 0 while M is -inf
-      const float w = __builtin_amdgcn_exp2f(ms - Mn) * ls; // 0 for an empty split
-      L = L * a + w;
+    for (int s0 = g; s0 < n_splits; s0 += BATCH * GROUPS) {
+      float ms[BATCH], ls[BATCH], v[BATCH][8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = acc[i] * a + w * v[i];
+      for (int k = 0; k < BATCH; ++k) {
+        const size_t pr = min(s0 + k * GROUPS, n_splits - 1) * stride + row;
+        ms[k] = p.ws_m[pr];
+        ls[k] = s0 + k * GROUPS < n_splits ? p.ws_l[pr] : 0.0f;
+        load_partial8(static_cast<const T*>(p.ws_o) + pr * kD + d0, v[k]);
+      }
+      float Mn = M;
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) Mn = fmaxf(Mn, ms[k]);
+      const float a = __builtin_amdgcn_exp2f(M - Mn);
       M = Mn;
+      L *= a;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] *= a;
+#pragma unroll
+      for (int k = 0; k < BATCH; ++k) {
+        const float w = __builtin_amdgcn_exp2f(ms[k] - Mn) * ls[k];
+        L += w;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += w * v[k][i];
+      }
     }
   }
   if constexpr (GROUPS > 1) {
@@ -1398,7 +1328,6 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
     for (int gg = 1; gg < GROUPS; ++gg) {
       const MergeState& o = s_st[threadIdx.x + 16 * gg];
       const float Mn = fmaxf(M, o.m);
-      if (Mn == -INFINITY) continue;
       const float a = __builtin_amdgcn_exp2f(M - Mn);
       const float w = __builtin_amdgcn_exp2f(o.m - Mn);
       L = L * a + w * o.l;
@@ -1444,27 +1373,6 @@ __global__ __launch_bounds__(kThreads) void merge_state_kernel(int rows, int D, 
   if (threadIdx.x == 0) lse_out[row] = lse;
 }
 
-Params make_params(const d2sd_attn_args& a, const AttnPlan& plan, void* ws) {
-  Params p{};
-  p.q = a.q; p.k_cache = a.k_cache; p.v_cache = a.v_cache; p.page_table = a.page_table;
-  p.ctx_len = a.ctx_len; p.k_tree = a.k_tree; p.v_tree = a.v_tree; p.node_indptr = a.node_indptr;
-  p.anc_mask = a.anc_mask; p.out = a.out; p.lse = a.lse;
-  const size_t rows = (size_t)a.total_nodes * a.num_qo_heads;
-  // [normalised O in the input dtype][m][l] (fp32), each split-major
-  char* w = static_cast<char*>(ws);
-  const size_t o_bytes = (size_t)plan.n_ch_max * rows * kD * (a.dtype == D2SD_BF16 ? 2 : 4);
-  p.ws_o = w;
-  p.ws_m = w ? reinterpret_cast<float*>(w + o_bytes) : nullptr;
-  p.ws_l = w ? p.ws_m + (size_t)plan.n_ch_max * rows : nullptr;
-  p.batch = a.batch; p.hq = a.num_qo_heads; p.hkv = a.num_kv_heads; p.G = plan.G; p.stage = a.stage;
-  p.total_nodes = a.total_nodes; p.max_nodes = a.max_nodes; p.max_ctx = a.max_ctx_len;
-  p.num_pages = a.num_pages; p.max_pages = a.max_pages; p.mask_words = a.mask_words;
-  p.split = plan.split; p.n_ch_max = plan.n_ch_max; p.n_rg_max = plan.n_rg_max;
-  p.items = (int)plan.items;
-  p.c2 = plan.scale * kLog2e;
-  return p;
-}
-
 }  // namespace
 
 hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& plan, void* ws,
@@ -1472,7 +1380,9 @@ hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& pla
   const Params p = make_params(a, plan, ws);
   const int grid = (int)(((plan.items + 7) / 8) * 8);
   if (ev[0]) (void)hipEventRecord(ev[0], stream);
-  if (a.dtype == D2SD_BF16 && plan.packed) {
+  if (plan.workgroups > 0) {
+    (void)launch_balanced_attention(a, plan, ws, stream);
+  } else if (a.dtype == D2SD_BF16 && plan.packed) {
     const long long wgs = (plan.tiles + pk::WAVES - 1) / pk::WAVES;
     const int pgrid = (int)(((wgs + 7) / 8) * 8);
     hipLaunchKernelGGL(cascade_bf16_packed_kernel, dim3(pgrid), dim3(pk::THREADS), 0, stream, p);
@@ -1485,7 +1395,7 @@ hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& pla
   if (ev[1]) (void)hipEventRecord(ev[1], stream);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && plan.n_ch_max > 1) {
-    const int groups = merge_groups(plan.n_ch_max);
+    const int groups = plan.merge_groups;
     const long long chunks = merge_chunks_per_request(a.max_nodes, a.num_qo_heads, groups);
     const dim3 mgrid((unsigned)(a.batch * chunks));
     if (a.dtype == D2SD_BF16) {
@@ -1510,6 +1420,7 @@ hipError_t launch_noncascade_attention(const d2sd_attn_args& a, float scale, hip
   AttnPlan plan{};
   plan.G = a.num_qo_heads / a.num_kv_heads;
   plan.waves = kBf16Waves;
+  plan.workgroups = 0;
   plan.packed = false;
   plan.tiles = 0;
   plan.split = 1 << 30;  // whole context in one pass

@@ -30,10 +30,12 @@ __device__ __forceinline__ uint32_t range_bits(int lo, int hi, int w) {
 struct AttnPlan {
   int G;             // query heads per KV head
   int waves;         // waves (query tiles) per workgroup: 4, or 12 for the wide bf16 shapes
+  int workgroups;    // balanced shape: its grid; 0 for the shapes with fixed splits
+  int merge_groups;  // thread groups per row of the split merge
   bool packed;       // 12 waves over the global tile sequence (several streams per workgroup)
   long long tiles;   // packed: query tiles of all streams (the grid holds ceil(tiles / 12) workgroups)
   int split;         // context tokens per split (multiple of 64)
-  int n_ch_max;      // splits of the longest context (>= 1)
+  int n_ch_max;      // splits of the longest context (>= 1); balanced: most pieces of a stream
   int n_rg_max;      // row groups of the largest request (>= 1)
   long long items;   // batch * hkv * n_ch_max * n_rg_max
   size_t ws_bytes;   // partial-state workspace (0 when n_ch_max == 1)
@@ -45,6 +47,9 @@ struct AttnPlan {
 // the call launches no merge (the caller then times the main kernel only).
 hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& plan, void* ws,
                                     hipStream_t stream, hipEvent_t (&ev)[3]);
+
+// The balanced kernel alone (launch_cascade_attention adds the split merge).
+hipError_t launch_balanced_attention(const d2sd_attn_args& a, const AttnPlan& plan, void* ws, hipStream_t stream);
 
 hipError_t launch_noncascade_attention(const d2sd_attn_args& a, float scale, hipStream_t stream,
                                        hipEvent_t (&ev)[3]);
@@ -74,15 +79,30 @@ constexpr int kPackedMinTiles = 6;
 constexpr int kPackedMaxBatch = 2048;
 constexpr int kPackedMaxSplit = 16384;
 
+// The balanced kernel: requests whose costs fit its LDS scan, and the cost
+// units of its division (a quarter of a round of one query tile per SIMD):
+// the least a key tile costs and the start and end of a stream.
+constexpr int kBalancedMaxBatch = 256;
+constexpr int kBalWaves = 12;
+constexpr int kBalWorkgroups = 256;  // one per CU
+constexpr int kBalMinCostBf16 = 8;
+constexpr int kBalOverheadBf16 = 72;
+constexpr int kBalMinCostF32 = 2;
+constexpr int kBalOverheadF32 = 8;
+constexpr int kBalMaxCost = 12;      // of a key tile: twelve query tiles
+
 // Rows (queries) per MFMA column tile. A work item's row group is one tile
 // per wave: 32 * plan.waves rows (fp32: always 4 waves).
 constexpr int kRowsPerTile = 32;
 
-// Split merge: 16 lanes per output row (8 dims each) and kMergeGroups(n)
-// groups of them per row, each folding every kMergeGroups-th split; a
-// workgroup of 256 threads then takes merge_rows(n) rows, and the grid is
-// batch x merge_chunks_per_request(...) workgroups.
-__host__ __device__ constexpr int merge_groups(int n_ch_max) { return n_ch_max >= 4 ? 4 : 1; }
+// Split merge: 16 lanes per output row (8 dims each) and 1 or 4 groups of them
+// per row, each folding every groups-th split; a workgroup of 256 threads then
+// takes merge_rows(groups) rows, and the grid is
+// batch x merge_chunks_per_request(...) workgroups. A group folds four splits
+// per round of loads, so four groups pay where a row has more than that: with
+// fixed splits from 4 on, in the balanced shape from 16 pieces of an average
+// stream on (one request of 33 pieces: 7.8 us against 10.5 with one group;
+// 16 requests of 2-4 pieces: 11.0 against 22.2).
 __host__ __device__ constexpr int merge_rows(int groups) { return 256 / (16 * groups); }
 __host__ __device__ inline long long merge_chunks_per_request(int max_nodes, int hq, int groups) {
   return ((long long)max_nodes * hq + merge_rows(groups) - 1) / merge_rows(groups);

@@ -1,0 +1,118 @@
+"""Verify attention over the even division of the batch's key tiles: batches
+that the automatic plan takes there, at the sizes where it can go wrong.
+
+The plan is the automatic one (no split, row group or packing asked for), so
+each case first checks that the partial-state size is the even division's (it
+has a count per stream, which the fixed splits do not)."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_04446_amd import workload as wl
+from tests.gpu_cases import Case, TOL, d2sd, max_abs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(lay, stages=(0,), host_offsets=True, reqs=None):
+    case = Case(lay, poison_slack=True)
+    rows = case.total * lay.spec.hq * (128 * (2 if case.dtype == "bf16" else 4) + 8)
+    assert d2sd().cascade_workspace_size(case._args(host_offsets=host_offsets)) % rows != 0, "not the even division"
+    for stage in stages:
+        o, l = case.attention(stage=stage, host_offsets=host_offsets)
+        torch.cuda.synchronize()
+        assert torch.isfinite(o.float()).all()
+        for b in range(lay.batch) if reqs is None else reqs:
+            s, e = int(case.node_indptr[b]), int(case.node_indptr[b + 1])
+            ow, lw = case.oracle_attention(b, ("cascade", "prefix", "tree")[stage])
+            lg = l[s:e].cpu().numpy()
+            fin = np.isfinite(lw)
+            assert np.array_equal(fin, np.isfinite(lg))
+            err = max(max_abs(o[s:e].double().cpu().numpy(), ow), max_abs(lg[fin], lw[fin]) if fin.any() else 0.0)
+            assert err <= TOL[case.dtype], (stage, b, err)
+
+
+def rows_for(rng, B, batch, k):
+    return [sorted(rng.choice(np.arange(1, B), int(rng.integers(0, k + 1)), replace=False).tolist()) for _ in range(batch)]
+
+
+# query tiles per stream from 1 to 13 (one and two row groups, 1 to 12 waves)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,p,hq,hkv", [(8, [], 8, 2), (16, [], 8, 2), (16, [4], 8, 2), (16, [1, 5, 9, 13], 32, 8),
+                                        (16, [1, 2, 3, 4, 5, 6], 8, 2), (24, [1, 2, 3, 4], 8, 2),
+                                        (32, [1, 2, 3], 8, 2), (32, [1, 2], 8, 1)])
+def test_query_tiles(B, p, hq, hkv, dtype):
+    check(wl.custom_layout(B, [p], [1100], hq=hq, hkv=hkv, dtype=dtype, seed=B + len(p)))
+
+
+# ends of key tiles, pages and ring fills; contexts shorter than the tree; empty ones
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("ctx", [[1024], [1025, 0, 1, 31], [1055, 32, 33, 63, 64, 65], [2047, 255, 256, 257, 511],
+                                 [1040, 1039, 1041, 16, 15, 17, 0, 0]])
+def test_ragged_contexts(ctx, dtype):
+    rng = np.random.default_rng(len(ctx))
+    check(wl.custom_layout(16, rows_for(rng, 16, len(ctx), 5), ctx, hq=8, hkv=2, dtype=dtype, seed=7), stages=(0, 1, 2),
+          host_offsets=False)
+
+
+def test_many_requests_and_shares_of_many_streams():
+    """One long context beside a hundred short ones (a workgroup takes many
+    streams; more requests than lanes of the scheduling wave), and the largest
+    batch the shape takes."""
+    rng = np.random.default_rng(5)
+    ctx = [6000] + [int(x) for x in rng.integers(0, 90, 100)]
+    check(wl.custom_layout(16, rows_for(rng, 16, 101, 2), ctx, hq=4, hkv=1, seed=8), reqs=range(0, 101, 7))
+    ctx = [1200] + [int(x) for x in rng.integers(0, 40, 255)]
+    check(wl.custom_layout(8, rows_for(rng, 8, 256, 1), ctx, hq=2, hkv=1, seed=9), reqs=range(0, 256, 17))
+
+
+def test_page_list_longer_than_one_staging():
+    """256 streams of 40,000 tokens: a workgroup's piece is longer than the
+    32,768 tokens whose page ids it stages at a time. The logical pages share
+    500 physical ones."""
+    lay = wl.custom_layout(8, [[]] * 16, [40000] * 16, hq=16, hkv=16, seed=3)
+    lay.page_table = np.random.default_rng(3).integers(0, 500, lay.page_table.shape).astype(np.int32)
+    lay.num_pages = 500
+    case = Case(lay)
+    o, l = case.attention(host_offsets=True)
+    torch.cuda.synchronize()
+    for b in (0, 15):
+        s, e = int(case.node_indptr[b]), int(case.node_indptr[b + 1])
+        ow, lw = case.oracle_attention(b)
+        assert max_abs(o[s:e].double().cpu().numpy(), ow) <= TOL["bf16"] and max_abs(l[s:e].cpu().numpy(), lw) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("scale", [30.0, 1000.0])
+def test_large_scores(scale):
+    """Scores far above the first tile's reference: the reference moves in the
+    middle of a stream, by more than the exponent range at the larger scale."""
+    lay = wl.custom_layout(16, [[3, 9], [1]], [1500, 1100], hq=8, hkv=2, seed=11)
+    case = Case(lay)
+    case.x["q"].mul_(scale)
+    o, l = case.attention(host_offsets=True)
+    torch.cuda.synchronize()
+    for b in range(2):
+        s, e = int(case.node_indptr[b]), int(case.node_indptr[b + 1])
+        ow, lw = case.oracle_attention(b)
+        # products of bf16 inputs are exact, their fp32 sums good to 1e-6 of a score of up to ~20 scale
+        tol = 2e-2 + 2e-5 * scale
+        assert max_abs(o[s:e].double().cpu().numpy(), ow) <= 2 * tol
+        assert max_abs(l[s:e].cpu().numpy(), lw) <= tol
+
+
+def test_two_streams_with_their_own_workspaces():
+    """Two calls in flight on two streams give what each gives alone."""
+    lays = [wl.custom_layout(16, [[3, 9], [1]], [3000, 1100], hq=8, hkv=2, seed=s) for s in (21, 22)]
+    cases = [Case(x) for x in lays]
+    alone = [c.attention(host_offsets=True) for c in cases]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    for _ in range(5):
+        got = []
+        for c, st in zip(cases, streams):
+            with torch.cuda.stream(st):
+                got.append(c.attention(host_offsets=True))
+        torch.cuda.synchronize()
+        for g, a in zip(got, alone):
+            assert torch.equal(g[0], a[0]) and torch.equal(g[1], a[1])
