@@ -35,20 +35,31 @@ constexpr int kMaxSteps = D2SD_MAX_VOCAB / (kWave * kLoadsPerStep * 4);   // fp3
 constexpr int kMaxNodes = D2SD_MAX_B + D2SD_MAX_B * (D2SD_MAX_B - 1) / 2;   // 2080
 constexpr int kNoIndex = 0x7fffffff;
 
+// 16 bytes at an address aligned to the element only: the row of an odd
+// vocabulary starts anywhere, and gfx9 global loads take any alignment.
+__device__ __forceinline__ uint4 load16(const void* p) {
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  struct __attribute__((packed)) Loose {
+    u32x4 v;
+  };
+  const u32x4 v = static_cast<const Loose*>(p)->v;
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+
 template <int DT>
 struct Logits;
 
 // The logits of elements start .. start + kVec - 1, still packed; elements at
 // or past V read as -inf. load_elems loads element by element at indices
 // clamped into the row, with no branch, so all loads of a step are issued
-// before any is used; load_raw takes one 16-byte load when the row is aligned
-// and the chunk lies inside it.
+// before any is used; load_raw takes one 16-byte load when the chunk lies
+// inside the row.
 template <>
 struct Logits<D2SD_BF16> {
   static constexpr int kVec = 8;
-  __device__ static __forceinline__ uint4 load_raw(const void* row, long long start, int V, bool vec_ok) {
+  __device__ static __forceinline__ uint4 load_raw(const void* row, long long start, int V) {
     const uint16_t* r = static_cast<const uint16_t*>(row);
-    if (vec_ok && start + kVec <= V) return *reinterpret_cast<const uint4*>(r + start);
+    if (start + kVec <= V) return load16(r + start);
     return load_elems(row, start, V);
   }
   __device__ static __forceinline__ uint4 load_elems(const void* row, long long start, int V) {
@@ -75,9 +86,9 @@ struct Logits<D2SD_BF16> {
 template <>
 struct Logits<D2SD_F32> {
   static constexpr int kVec = 4;
-  __device__ static __forceinline__ uint4 load_raw(const void* row, long long start, int V, bool vec_ok) {
+  __device__ static __forceinline__ uint4 load_raw(const void* row, long long start, int V) {
     const float* r = static_cast<const float*>(row);
-    if (vec_ok && start + kVec <= V) return *reinterpret_cast<const uint4*>(r + start);
+    if (start + kVec <= V) return load16(r + start);
     return load_elems(row, start, V);
   }
   __device__ static __forceinline__ uint4 load_elems(const void* row, long long start, int V) {
@@ -97,8 +108,8 @@ struct Logits<D2SD_F32> {
 };
 
 template <int DT>
-__device__ __forceinline__ void load_logits(const void* row, long long start, int V, bool vec_ok, float* v) {
-  Logits<DT>::unpack(Logits<DT>::load_raw(row, start, V, vec_ok), v);
+__device__ __forceinline__ void load_logits(const void* row, long long start, int V, float* v) {
+  Logits<DT>::unpack(Logits<DT>::load_raw(row, start, V), v);
 }
 
 // Cross-lane reductions and scans on DPP (inside rows of 16 lanes) and the
@@ -188,18 +199,20 @@ __device__ __forceinline__ int step_index(int s, int lane, int i) {
 }
 
 // Issue the loads of kResident whole steps of a wave (steps s0, s0 + waves,
-// ...) of an aligned row: plain 16-byte loads under a wave-uniform bound.
+// ...): plain 16-byte loads under a wave-uniform bound. A row of an odd
+// vocabulary starts anywhere; element by element it took three times as long.
 template <int DT>
 __device__ __forceinline__ void load_full(uint4 (&raw)[kResident][kLoadsPerStep], const void* rowp, int s0,
-                                          int n_full, int lane) {
+                                          int n_whole, int lane) {
   constexpr int VEC = Logits<DT>::kVec;
-  const uint4* r = static_cast<const uint4*>(rowp);
+  const char* r = static_cast<const char*>(rowp);
 #pragma unroll
   for (int j = 0; j < kResident; ++j) {
     const int s = s0 + j * kSampleWaves;
-    if (s < n_full) {
+    if (s < n_whole) {
 #pragma unroll
-      for (int k = 0; k < kLoadsPerStep; ++k) raw[j][k] = r[step_index<VEC>(s, lane, k * VEC) / VEC];
+      for (int k = 0; k < kLoadsPerStep; ++k)
+        raw[j][k] = load16(r + (size_t)step_index<VEC>(s, lane, k * VEC) * (16 / VEC));
     }
   }
 }
@@ -264,73 +277,77 @@ __global__ __launch_bounds__(kSampleThreads) void sample_targets_kernel(
   const int Nb = clampi(node_indptr[b + 1] - base, 0, min(kMaxNodes, total_nodes - base));
   if (c >= Nb) return;
 
-  // ---- representative: the lowest-index node with the same root path tokens
-  for (int x = t; x <= c; x += kSampleThreads) {
-    int par = parent[base + x];
-    if (par < 0 || par >= x) par = -1;          // parents precede children
-    s_par[x] = (short)par;
-    s_tok[x] = draft[base + x];
-  }
+  // ---- representative: the lowest-index node with the same root path tokens.
+  // Only a node with this node's own token can be one, and few trees hold it
+  // twice: the paths are looked at only where one does.
+  const int tok_c = draft[base + c];
+  bool twin = false;
+  for (int x = t; x < c; x += kSampleThreads) twin |= draft[base + x] == tok_c;
   // The node is usually its own representative: the first loads of its row go
-  // out now (after the staging above, whose wait would otherwise include
-  // them) and are in flight during the search below.
+  // out now (after the tokens above, whose wait would otherwise include them)
+  // and are in flight during the search below.
   const int n_steps = ceil_div(V, SE);
   const int n_whole = V / SE;                   // steps lying wholly inside the row
   const void* row_c = static_cast<const char*>(logits) + (size_t)(base + c) * (size_t)V * kEltBytes;
-  const bool vec_ok_c = ((size_t)(base + c) * (size_t)V) % VEC == 0;   // the row starts 16-byte aligned
   uint4 raw[kResident][kLoadsPerStep];
-  load_full<DT>(raw, row_c, w, vec_ok_c ? n_whole : 0, lane);
-  __syncthreads();
-  if (t == 0) {
-    int x = c, d = 0;
-    while (s_par[x] >= 0 && d < D2SD_MAX_B) {
-      s_path[d++] = s_tok[x];
-      x = s_par[x];
+  load_full<DT>(raw, row_c, w, n_whole, lane);
+  int rep = c;
+  if (__syncthreads_or(twin)) {
+    for (int x = t; x <= c; x += kSampleThreads) {
+      int par = parent[base + x];
+      if (par < 0 || par >= x) par = -1;          // parents precede children
+      s_par[x] = (short)par;
+      s_tok[x] = draft[base + x];
     }
-    s_walk[0] = s_par[x] >= 0 ? -1 : d;
-    s_walk[1] = x;
-  }
-  __syncthreads();
-  const int depth = s_walk[0], root = s_walk[1];
-  int best = c;
-  if (depth >= 0) {
-    for (int m = t; m < c; m += kSampleThreads) {
-      int x = m;
-      bool ok = true;
-      for (int i = 0; i < depth && ok; ++i) {
-        const int px = s_par[x];
-        ok = px >= 0 && s_tok[x] == s_path[i];
-        x = px;
+    __syncthreads();
+    if (t == 0) {
+      int x = c, d = 0;
+      while (s_par[x] >= 0 && d < D2SD_MAX_B) {
+        s_path[d++] = s_tok[x];
+        x = s_par[x];
       }
-      if (ok && x == root) best = min(best, m);   // x == root implies x is a root
+      s_walk[0] = s_par[x] >= 0 ? -1 : d;
+      s_walk[1] = x;
     }
-  }
-  best = wave_min(best);
-  if (lane == 0) s_best[w] = best;
-  __syncthreads();
-  int rep = s_best[0];
+    __syncthreads();
+    const int depth = s_walk[0], root = s_walk[1];
+    int best = c;
+    if (depth >= 0) {
+      for (int m = t; m < c; m += kSampleThreads) {
+        int x = m;
+        bool ok = true;
+        for (int i = 0; i < depth && ok; ++i) {
+          const int px = s_par[x];
+          ok = px >= 0 && s_tok[x] == s_path[i];
+          x = px;
+        }
+        if (ok && x == root) best = min(best, m);   // x == root implies x is a root
+      }
+    }
+    best = wave_min(best);
+    if (lane == 0) s_best[w] = best;
+    __syncthreads();
+    rep = s_best[0];
 #pragma unroll
-  for (int i = 1; i < kSampleWaves; ++i) rep = min(rep, s_best[i]);
+    for (int i = 1; i < kSampleWaves; ++i) rep = min(rep, s_best[i]);
+  }
 
   // ---- one pass over the representative's row: per-step (max, sum) or (max, index)
   const size_t row = (size_t)(base + rep);
   const void* rowp = static_cast<const char*>(logits) + row * (size_t)V * kEltBytes;
-  const bool vec_ok = (row * (size_t)V) % VEC == 0;
-  // A wave takes steps w, w + 4, ...: the whole steps of an aligned row in
-  // batches of kResident whose loads are issued together, then the rest (a
-  // ragged last step, or every step of an unaligned row) element by element.
-  const int n_full = vec_ok ? n_whole : 0;
-  if (rep != c) load_full<DT>(raw, rowp, w, n_full, lane);
-  for (int s0 = w; s0 < n_full; s0 += kSampleWaves * kResident) {
-    if (s0 != w) load_full<DT>(raw, rowp, s0, n_full, lane);
+  // A wave takes steps w, w + 4, ...: the whole steps in batches of kResident
+  // whose loads are issued together, then a ragged last step element by element.
+  if (rep != c) load_full<DT>(raw, rowp, w, n_whole, lane);
+  for (int s0 = w; s0 < n_whole; s0 += kSampleWaves * kResident) {
+    if (s0 != w) load_full<DT>(raw, rowp, s0, n_whole, lane);
 #pragma unroll
     for (int j = 0; j < kResident; ++j) {
       const int s = s0 + j * kSampleWaves;
-      if (s < n_full) reduce_step<DT>(raw[j], s, lane, greedy, k2, s_m, s_x);
+      if (s < n_whole) reduce_step<DT>(raw[j], s, lane, greedy, k2, s_m, s_x);
     }
   }
   for (int s = w; s < n_steps; s += kSampleWaves) {
-    if (s < n_full) continue;
+    if (s < n_whole) continue;
     uint4 tail[kLoadsPerStep];
 #pragma unroll
     for (int k = 0; k < kLoadsPerStep; ++k)
@@ -387,7 +404,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_targets_kernel(
       float v[NE];
 #pragma unroll
       for (int k = 0; k < kLoadsPerStep; ++k)
-        load_logits<DT>(rowp, (long long)step_index<VEC>(sel, lane, k * VEC), V, vec_ok, v + k * VEC);
+        load_logits<DT>(rowp, (long long)step_index<VEC>(sel, lane, k * VEC), V, v + k * VEC);
       const float ms = s_m[sel];
       const float moff = step_offset(ms, k2);
       const float scale = step_scale(ms, mx, k2);

@@ -279,3 +279,45 @@ def test_sampled_verify_matches_oracle(cfg):
         off += tr.N
     if layout.batch >= 8:                      # one request may reject at its first draft
         assert accepted > 0
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [2049, 4103, 8191, 16421])
+def test_rows_at_any_alignment(dtype, V):
+    """Rows of an odd vocabulary start at every element alignment: the argmax
+    planted at the ends of the 16-byte chunks, of the steps and of the row is
+    found, and a draw equals the same draw from a copy of the row that starts
+    aligned (same sums in the same order, so bit for bit)."""
+    m = d2sd()
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    n = 17
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    logits = torch.randn((n, V), generator=gen, device="cuda").to(dt)
+    spots = [0, 1, 7, 8, 511, 512, 1023, 1024, 2047, 2048, V - 9, V - 8, V - 2, V - 1, V // 2, V // 3, 5]
+    for r, x in enumerate(spots):
+        logits[r, x] = 20.0
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    ip, parent, draft = i32([0, n]), i32([-1] + list(range(n - 1))), i32(list(range(100, 100 + n)))
+    tok, _ = m.sample_targets(ip, n, n, parent, draft, logits, 0.0)
+    assert tok.cpu().tolist() == spots
+    logits[:, :] = torch.randn((n, V), generator=gen, device="cuda").to(dt)
+    u = torch.rand(n, generator=gen, device="cuda")
+    tok, _ = m.sample_targets(ip, n, n, parent, draft, logits, 1.0, uniform=u)
+    one, z = i32([0, 1]), i32([-1])
+    for r in range(n):
+        alone, _ = m.sample_targets(one, 1, 1, z, draft[r:r + 1].clone(), logits[r:r + 1].clone(), 1.0, uniform=u[r:r + 1].clone())
+        assert alone.item() == tok[r].item(), r
+
+
+def test_equal_tokens_on_different_paths_keep_their_own_draws():
+    """A token that occurs twice makes a node look at the root paths; only an
+    equal path shares the draw."""
+    m = d2sd()
+    i32 = lambda v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    #        0   1   2   3 (twin of 1)  4 (child of 3, token of 2: twin of 2)  5 (token of 1 under 2)  6 (token of 2 under 5)
+    parent = i32([-1, 0, 1, 0, 3, 2, 5])
+    draft = i32([9, 11, 12, 11, 12, 11, 12])
+    logits = torch.randn((7, 3000), device="cuda")
+    tok, rep = m.sample_targets(i32([0, 7]), 7, 7, parent, draft, logits, 0.0, want_rep=True)
+    assert rep.cpu().tolist() == [0, 1, 2, 1, 2, 5, 6]
+    assert tok.cpu().tolist() == logits.argmax(1)[torch.tensor([0, 1, 2, 1, 2, 5, 6], device="cuda")].cpu().tolist()
