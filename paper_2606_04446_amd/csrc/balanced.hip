@@ -151,7 +151,6 @@ __device__ __forceinline__ int fresh(int x) {
 }
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ int lane_of(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
 
 // Wait until at most `tiles` of the wave's later tile copies (2 * COPIES DMAs
 // each) are outstanding; sync_tiles: and all its LDS reads done, then the
@@ -516,24 +515,6 @@ struct BalShared {
   int share, end;       // cost units per workgroup; where this one's share ends
   BalPiece piece[2];
 };
-
-// Inclusive sum (and, with MAX, running maximum) over the lanes of a wave:
-// inside rows of 16 by DPP shifts, then across rows by DPP broadcasts.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ int dpp0(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);
-}
-template <bool MAX>
-__device__ __forceinline__ int wave_scan(int x) {           // x >= 0
-  auto op = [](int a, int b) { return MAX ? max(a, b) : a + b; };
-  x = op(x, dpp0<0x111, 0xf>(x));
-  x = op(x, dpp0<0x112, 0xf>(x));
-  x = op(x, dpp0<0x114, 0xf>(x));
-  x = op(x, dpp0<0x118, 0xf>(x));
-  x = op(x, dpp0<0x142, 0xa>(x));
-  x = op(x, dpp0<0x143, 0xc>(x));
-  return x;
-}
 
 // The workgroup's first piece at or after stream sidx of request b, and the
 // stream's share limits; written to `out` by lane 0.

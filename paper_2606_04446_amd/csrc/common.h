@@ -17,6 +17,27 @@ constexpr int kWave = 64;
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 __host__ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Inclusive scan (sum, or running maximum) of values >= 0 over the lanes of a
+// wave: inside rows of 16 by DPP shifts, then across rows by DPP broadcasts,
+// register to register. Every lane has to be active.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int dpp0(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, false);
+}
+template <bool MAX>
+__device__ __forceinline__ int wave_scan(int x) {
+  auto op = [](int a, int b) { return MAX ? max(a, b) : a + b; };
+  x = op(x, dpp0<0x111, 0xf>(x));
+  x = op(x, dpp0<0x112, 0xf>(x));
+  x = op(x, dpp0<0x114, 0xf>(x));
+  x = op(x, dpp0<0x118, 0xf>(x));
+  x = op(x, dpp0<0x142, 0xa>(x));
+  x = op(x, dpp0<0x143, 0xc>(x));
+  return x;
+}
+// The value of lane `src`.
+__device__ __forceinline__ int lane_of(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
+
 // Bits [lo, hi) of a bit set restricted to word w (bits 32w .. 32w+31).
 __device__ __forceinline__ uint32_t range_bits(int lo, int hi, int w) {
   const int a = max(lo, 32 * w) - 32 * w;
