@@ -14,6 +14,7 @@ namespace d2sd {
 namespace {
 
 constexpr int kTreeThreads = 256;
+constexpr int kMaxNodes = D2SD_MAX_B + D2SD_MAX_B * (D2SD_MAX_B - 1) / 2;  // 2080
 
 __global__ __launch_bounds__(kTreeThreads) void tree_build_kernel(
     int B, int Kmax, const int* __restrict__ K, const int* __restrict__ p,
@@ -88,48 +89,54 @@ __global__ __launch_bounds__(kTreeThreads) void tree_build_kernel(
 // third-level cascade and resampled chains. Node n walks its parent links,
 // setting one mask bit per ancestor-or-self and counting the depth; a parent
 // outside [0, n) makes n a root of its own. path_id[n] counts the nodes m in
-// 1..n whose parent is not m - 1 (path starts), by a chunked block scan.
+// 1..n whose parent is not m - 1 (path starts).
+//
+// Latency-bound: a walk is as long as the node's depth. The links are staged
+// in LDS, and as they only lead to smaller indexes, the mask words are filled
+// from the highest down in a register and stored once each. The path starts
+// are counted by ballot, kTreeThreads nodes at a time, with one barrier.
+// 16 requests of 48-80 nodes: 6.0 us with links and masks walked in memory,
+// 5.5 us now; one request: 5.4 -> 3.4 us.
 __global__ __launch_bounds__(kTreeThreads) void tree_from_parents_kernel(
     const int* __restrict__ node_indptr, int total_nodes, int max_nodes, int mask_words,
     const int* __restrict__ parent, int* __restrict__ depth, int* __restrict__ path_id,
     uint32_t* __restrict__ anc_mask) {
-  __shared__ int s_scan[kTreeThreads];
-  __shared__ int s_carry;
+  __shared__ short s_par[kMaxNodes];
+  __shared__ int s_starts[2][kTreeThreads / kWave];
   const int b = blockIdx.x;
   const int t = threadIdx.x;
+  const int lane = t % kWave, wave = t / kWave;
   const int base = clampi(node_indptr[b], 0, total_nodes);
   const int Nb = clampi(node_indptr[b + 1] - base, 0, min(max_nodes, total_nodes - base));
-  auto par_of = [&](int n) {
-    const int q = parent[base + n];
-    return (q >= 0 && q < n) ? q : -1;
-  };
+  int carry = 0;
+  for (int n0 = 0, odd = 0; n0 < Nb; n0 += kTreeThreads, odd ^= 1) {
+    const int n = n0 + t;
+    const int q = n < Nb ? parent[base + n] : -1;
+    if (n < Nb) s_par[n] = (short)(q >= 0 && q < n ? q : -1);
+    const unsigned long long starts = __ballot(n > 0 && n < Nb && q != n - 1);
+    if (lane == 0) s_starts[odd][wave] = __popcll(starts);
+    __syncthreads();
+    int id = carry + __popcll(starts & (~0ull >> (kWave - 1 - lane)));
+#pragma unroll
+    for (int w = 0; w < kTreeThreads / kWave; ++w) {
+      if (w < wave) id += s_starts[odd][w];
+      carry += s_starts[odd][w];
+    }
+    if (n < Nb) path_id[base + n] = id;
+  }
+  // every link is in LDS: the last chunk's barrier
   for (int n = t; n < Nb; n += kTreeThreads) {
     uint32_t* row = anc_mask + (size_t)(base + n) * mask_words;
-    for (int w = 0; w < mask_words; ++w) row[w] = 0u;
-    int d = -1;
-    for (int a = n; a >= 0; a = par_of(a)) {
-      row[a >> 5] |= 1u << (a & 31);
-      ++d;
+    int d = -1, a = n;
+    for (int w = mask_words - 1; w >= 0; --w) {
+      uint32_t bits = 0u;
+      for (; a >= 32 * w; a = s_par[a]) {
+        bits |= 1u << (a & 31);
+        ++d;
+      }
+      row[w] = bits;
     }
     depth[base + n] = d;
-  }
-  if (t == 0) s_carry = 0;
-  __syncthreads();
-  for (int n0 = 0; n0 < Nb; n0 += kTreeThreads) {
-    const int n = n0 + t;
-    s_scan[t] = (n > 0 && n < Nb && parent[base + n] != n - 1) ? 1 : 0;
-    __syncthreads();
-    for (int dd = 1; dd < kTreeThreads; dd <<= 1) {
-      const int v = t >= dd ? s_scan[t - dd] : 0;
-      __syncthreads();
-      s_scan[t] += v;
-      __syncthreads();
-    }
-    const int carry = s_carry;
-    if (n < Nb) path_id[base + n] = carry + s_scan[t];
-    __syncthreads();
-    if (t == kTreeThreads - 1) s_carry = carry + s_scan[t];
-    __syncthreads();
   }
 }
 

@@ -136,3 +136,34 @@ def test_attention_and_accept_on_general_trees(shape, dtype):
         assert int(acc["best_path"][b]) == a.best_path
         pn, tk = a.padded(B)
         assert acc["path_nodes"][b].cpu().tolist() == pn and acc["out_tokens"][b].cpu().tolist() == tk
+
+
+@pytest.mark.parametrize("N", [1, 2, 63, 64, 65, 255, 256, 257, 513, 2080])
+@pytest.mark.parametrize("shape", ["chain", "star", "links_out_of_range"])
+def test_builder_at_the_edges_of_waves_and_chunks(N, shape):
+    """Whole numbers, so compared bit for bit: nodes around a wave and a chunk of
+    256, the deepest and the widest tree, and links that make roots of their own."""
+    m = d2sd()
+    dev = torch.device("cuda")
+    n = np.arange(N)
+    raw = {"chain": n - 1, "star": np.zeros(N, int), "links_out_of_range": np.where(n % 7 == 3, n + n % 5 - 2, n - 1)}[shape]
+    raw[0] = -1
+    raw = np.concatenate([raw, raw[: N // 2 + 1]]).astype(np.int32)      # and a second, smaller tree
+    ip = np.array([0, N, N + N // 2 + 1], np.int32)
+    W = (N + 31) // 32 + 1                                               # one word more than needed
+    got = m.tree_from_parents(torch.from_numpy(ip).to(dev), int(ip[-1]), N, torch.from_numpy(raw).to(dev), W)
+    depth = np.zeros(len(raw), np.int32)
+    path = np.zeros(len(raw), np.int32)
+    mask = np.zeros((len(raw), 32 * W), bool)
+    for base, end in zip(ip[:-1], ip[1:]):
+        for i in range(end - base):
+            q = raw[base + i] if 0 <= raw[base + i] < i else -1
+            if q >= 0:
+                depth[base + i] = depth[base + q] + 1
+                mask[base + i] = mask[base + q]
+            mask[base + i, i] = True
+            path[base + i] = (path[base + i - 1] if i else 0) + int(i > 0 and raw[base + i] != i - 1)
+    words = np.packbits(mask, axis=1, bitorder="little").view(np.int32)
+    assert np.array_equal(got["depth"].cpu().numpy(), depth)
+    assert np.array_equal(got["path_id"].cpu().numpy(), path)
+    assert np.array_equal(got["anc_mask"].cpu().numpy().reshape(words.shape), words)
