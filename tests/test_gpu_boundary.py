@@ -140,3 +140,22 @@ def test_select_then_tree_on_device_matches_oracle():
     assert np.array_equal(tree["path_id"].cpu().numpy(), path)
     assert np.array_equal(tree["anc_mask"].cpu().numpy(), mask)
     assert np.array_equal(tree["path_leaf"].cpu().numpy(), leaf)
+
+
+@pytest.mark.parametrize("B,Kmax", [(2, 1), (16, 7), (16, 9), (16, 20), (64, 63)])
+def test_tree_indptr_row_lengths(B, Kmax):
+    """Rows of p around the eight entries loaded at a time, with entries past K
+    that must not count and more columns than a block has positions."""
+    m = d2sd()
+    rng = np.random.default_rng([B, Kmax])
+    batch, most = 300, min(Kmax, B - 1)
+    K = rng.integers(0, most + 1, size=batch).astype(np.int32)
+    K[:2] = most, 0
+    p = rng.integers(1, B, size=(batch, Kmax)).astype(np.int32)
+    for b in range(batch):
+        p[b, :K[b]] = rng.choice(np.arange(1, B), size=K[b], replace=False)
+    want = np.concatenate([[0], np.cumsum([B + sum(B - int(x) for x in p[b, :K[b]]) for b in range(batch)])])
+    dev = torch.device("cuda")
+    ip = m.tree_indptr(B, torch.from_numpy(K).to(dev), torch.from_numpy(p).to(dev))
+    torch.cuda.synchronize()
+    assert np.array_equal(ip.cpu().numpy(), want)
