@@ -266,7 +266,8 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
   const long long key_tiles = ((long long)a->max_ctx_len + 31) / 32 + ((long long)a->max_nodes + 31) / 32 + 1;
   const long long query_tiles = ((long long)a->max_nodes * G + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile;
   const long long groups = (query_tiles + d2sd::kBalWaves - 1) / d2sd::kBalWaves;
-  const long long stream = key_tiles * d2sd::kBalMaxCost + d2sd::kBalOverheadBf16;
+  const int top = a->dtype == D2SD_F32 ? d2sd::kBalMaxCostF32 : d2sd::kBalMaxCostBf16;
+  const long long stream = key_tiles * top + d2sd::kBalOverheadBf16;
   if (stream * kNumCUs > (1ll << 30)) return 0;
   if (stream * groups * a->num_kv_heads > (1ll << 30) / a->batch) return 0;
   return d2sd::kBalWorkgroups;

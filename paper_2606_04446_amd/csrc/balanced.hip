@@ -38,7 +38,7 @@
 // Attention time with the split merge (launch events included), fixed splits
 // before: 1 request of 32k tokens 83 -> 56 us (of which the kernel moves its
 // 134 MB at 3.6 TB/s); 8 of 1k-8k 103 -> 72; 16 of 0-8k without host offsets
-// 195 -> 135; fp32, 4 of 300-3000, 225 -> 99 (52 TFLOP/s in the products).
+// 195 -> 131; fp32, 4 of 300-3000, 225 -> 99 (52 TFLOP/s in the products).
 // A call on little work is bound by its start: about 3 us until a workgroup
 // has its piece, 2 until the query rows and page ids are there, 4 until the
 // first tiles of all CUs have arrived, 2 for the stores.
@@ -71,10 +71,18 @@ struct BalTile<__bf16> {
   static constexpr int MAX_KG = 1;
   static constexpr int STEP = 2;                               // key tiles per step and key group
   static constexpr int COPIES = 1;                             // 1 KB K (and V) blocks per copy wave and tile
-  // Cost units: a quarter of a round of one query tile per SIMD. A tile's 16 KB
-  // take about as long to arrive from HBM as eight query tiles to be computed.
+  // What a key tile costs beside `tiles` query tiles, in units of 0.056 us
+  // (0.064 from HBM). Measured per key tile and CU, of 8 and 16 requests from
+  // the Infinity Cache and from HBM, in us: 1-4 query tiles 0.57 / 0.71 (the
+  // arrival of its 16 KB), 5 0.80 / 0.93, 6 0.81 / 1.00, 7 0.87 / 1.08,
+  // 8 0.95 / 1.15, 9 1.18 / 1.34, 10 1.25 / 1.36, 12 1.35 / 1.55: a step for
+  // each query tile that a SIMD's waves take in turn, and less for each tile.
+  // Counted as whole rounds (8, 8, 12 for up to 4, 8 and 12 tiles), CUs whose
+  // requests had few tiles waited for the others: 16 requests of 0-8k tokens
+  // and 40-110 nodes took 123.1 us (mean of eight batches), now 119.6.
+  __device__ static __forceinline__ int cost(int tiles, int) { return max(MIN_COST, tiles + 3 * ((tiles + 3) >> 2) + 3); }
   static constexpr int MIN_COST = kBalMinCostBf16;
-  static constexpr int OVERHEAD = kBalOverheadBf16;            // start and end of a stream, in the same units
+  static constexpr int OVERHEAD = kBalOverheadBf16;            // start and end of a stream, about 9 us (96: 5% slower, 144-256 level)
 };
 template <>
 struct BalTile<float> {
@@ -86,8 +94,12 @@ struct BalTile<float> {
   static constexpr int MAX_KG = 2;
   static constexpr int STEP = 1;
   static constexpr int COPIES = 2;
-  static constexpr int MIN_COST = kBalMinCostF32;              // fp32 MFMA bound: only the query tiles count
-  static constexpr int OVERHEAD = kBalOverheadF32;
+  // fp32 is MFMA bound: a quarter of a round of one query tile per SIMD.
+  __device__ static __forceinline__ int cost(int tiles, int kg) {
+    return max(MIN_COST, kg == 1 ? (tiles + 3) & ~3 : 2 * ((tiles + 1) >> 1));
+  }
+  static constexpr int MIN_COST = kBalMinCostF32;
+  static constexpr int OVERHEAD = kBalOverheadF32;             // against 8: 4 requests of 300-3000 tokens 93.7 -> 92.0 us
 };
 
 // Sizes of one request and what they cost.
@@ -97,7 +109,7 @@ struct BalReq {
   int kg;               // key groups
   int n_ctx, n_tiles;   // context key tiles, all key tiles
   int cost;             // per key tile
-  int stream;           // per stream: overhead + max(n_tiles, 1) * cost
+  int work;             // per stream, without its start: max(n_tiles, 1) * cost
   int streams;          // hkv * rg (0: no rows)
 };
 
@@ -124,8 +136,8 @@ __device__ __forceinline__ BalReq bal_request(const Params& p, int node_base, in
   r.kg = BT::MAX_KG == 2 && r.tpg <= bal::WAVES / 2 ? 2 : 1;
   r.n_ctx = p.stage != D2SD_STAGE_TREE ? ceil_div(C, bal::KT) : 0;
   r.n_tiles = r.n_ctx + (p.stage != D2SD_STAGE_PREFIX ? ceil_div(Nb, bal::KT) : 0);
-  r.cost = max(BT::MIN_COST, r.kg == 1 ? (r.tpg + 3) & ~3 : 2 * ((r.tpg + 1) >> 1));
-  r.stream = BT::OVERHEAD + max(1, r.n_tiles) * r.cost;
+  r.cost = BT::cost(r.tpg, r.kg);
+  r.work = max(1, r.n_tiles) * r.cost;
   r.streams = r.T > 0 ? p.hkv * r.rg : 0;
   return r;
 }
@@ -512,7 +524,9 @@ struct BalShared {
   int pid[2 * bal::CHUNK_TILES + 8];
   int pref[bal::MAX_BATCH + 1];
   int node[bal::MAX_BATCH], nb[bal::MAX_BATCH], ctx[bal::MAX_BATCH];
+  int streams[bal::MAX_BATCH];   // of the requests before, within the scheduling lane
   int share, end;       // cost units per workgroup; where this one's share ends
+  int start;            // what the start of a stream costs
   BalPiece piece[2];
 };
 
@@ -521,18 +535,17 @@ struct BalShared {
 template <typename T>
 __device__ __forceinline__ void bal_seek(const Params& p, const BalShared<T>& sh, int batch, int b, int sidx,
                                          BalPiece& out, int lane) {
-  using BT = BalTile<T>;
   const int item = blockIdx.x;
-  const int share = uni(sh.share), hi = uni(sh.end);
+  const int share = uni(sh.share), hi = uni(sh.end), start = uni(sh.start);
   BalPiece pc{};
   for (; b < batch;) {
     const int base = uni(sh.pref[b]);
     if (base >= hi) break;
     const BalReq rq = bal_request<T>(p, uni(sh.node[b]), uni(sh.nb[b]), uni(sh.ctx[b]));
     for (; sidx < rq.streams; ++sidx) {
-      const int s0 = base + sidx * rq.stream;
+      const int s0 = base + sidx * (start + rq.work);
       if (s0 >= hi) break;
-      const int x0 = s0 + BT::OVERHEAD;                     // cost position of tile 0
+      const int x0 = s0 + start;                            // cost position of tile 0
       const int n = max(1, rq.n_tiles);
       const int i0 = uni(quick_div(x0, share)), i1 = uni(quick_div(x0 + (n - 1) * rq.cost, share));
       if (item < i0 || item > i1) continue;
@@ -571,7 +584,7 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
     end[k] = in ? p.node_indptr[b + 1] : 0;
     ctx[k] = in ? p.ctx_len[b] : 0;
   }
-  int sum = 0, top_cost = 1, top_work = 0;
+  int sum = 0, count = 0, top_cost = 1, top_work = 0;
   int cost[bal::PER_LANE];
   for (int k = 0; k < per; ++k) {
     const int b = lane * per + k;
@@ -586,13 +599,18 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
     if (b < batch) {
       sh.node[b] = nd; sh.nb[b] = Nb; sh.ctx[b] = C;
       sh.pref[b] = sum;
+      sh.streams[b] = count;
     }
-    sum += r.streams * r.stream;
+    sum += r.streams * r.work;
+    count += r.streams;
     top_cost = max(top_cost, r.streams ? r.cost : 1);
     top_work = max(top_work, r.streams ? r.n_tiles * r.cost : 0);
   }
-  const int incl = wave_scan<false>(sum);
-  const int total = lane_of(incl, 63);
+  // The start of a stream counts as four shares of the tiles at most: where
+  // shares are short, more would leave workgroups without any tile.
+  const int incl = wave_scan<false>(sum), incl_count = wave_scan<false>(count);
+  const int start = min(BalTile<T>::OVERHEAD, 4 * ceil_div(lane_of(incl, 63), kBalWorkgroups));
+  const int total = lane_of(incl, 63) + start * lane_of(incl_count, 63);
   // A share is at least one tile (every piece then holds a tile) and long
   // enough that no stream falls into more than n_ch_max pieces.
   int share = max(ceil_div(total, kBalWorkgroups), lane_of(wave_scan<true>(top_cost), 63));
@@ -601,6 +619,7 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
   const int lo = (int)blockIdx.x * share;
   if (lane == 0) {
     sh.share = share;
+    sh.start = start;
     sh.end = min(lo + share, total);
   }
   // the request that holds cost position lo
@@ -608,7 +627,7 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
   for (int k = 0; k < per; ++k) {
     const int b = lane * per + k;
     if (b >= batch) break;
-    const int before = sh.pref[b] + incl - sum;
+    const int before = sh.pref[b] + incl - sum + start * (sh.streams[b] + incl_count - count);
     sh.pref[b] = before;
     if (before <= lo) at = b;
   }
@@ -620,7 +639,7 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
   // requests without rows cost nothing: the last one that starts at or before lo holds it
   const int b = lane_of(wave_scan<true>(at + 1), 63) - 1;
   const BalReq rq = bal_request<T>(p, uni(sh.node[b]), uni(sh.nb[b]), uni(sh.ctx[b]));
-  bal_seek<T>(p, sh, batch, b, uni(quick_div(lo - uni(sh.pref[b]), rq.stream)), sh.piece[0], lane);
+  bal_seek<T>(p, sh, batch, b, uni(quick_div(lo - uni(sh.pref[b]), start + rq.work)), sh.piece[0], lane);
 }
 
 // Key tiles [t0, t1) of the piece's stream, page ids of the context ones

@@ -101,16 +101,17 @@ constexpr int kPackedMaxBatch = 2048;
 constexpr int kPackedMaxSplit = 16384;
 
 // The balanced kernel: requests whose costs fit its LDS scan, and the cost
-// units of its division (a quarter of a round of one query tile per SIMD):
-// the least a key tile costs and the start and end of a stream.
+// units of its division: the least a key tile costs, the most (twelve query
+// tiles), and the start and end of a stream.
 constexpr int kBalancedMaxBatch = 256;
 constexpr int kBalWaves = 12;
 constexpr int kBalWorkgroups = 256;  // one per CU
-constexpr int kBalMinCostBf16 = 8;
-constexpr int kBalOverheadBf16 = 72;
+constexpr int kBalMinCostBf16 = 11;
+constexpr int kBalMaxCostBf16 = 24;
+constexpr int kBalOverheadBf16 = 160;
 constexpr int kBalMinCostF32 = 2;
-constexpr int kBalOverheadF32 = 8;
-constexpr int kBalMaxCost = 12;      // of a key tile: twelve query tiles
+constexpr int kBalMaxCostF32 = 12;
+constexpr int kBalOverheadF32 = 12;
 
 // Rows (queries) per MFMA column tile. A work item's row group is one tile
 // per wave: 32 * plan.waves rows (fp32: always 4 waves).
