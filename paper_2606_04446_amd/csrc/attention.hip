@@ -1284,7 +1284,8 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
   const int row = node_base * p.hq + r;
   const size_t stride = (size_t)p.total_nodes * p.hq;
   // A group folds BATCH of its splits at a time: their loads go out together,
-  // the last ones repeated with weight 0. The reference starts below every
+  // those past the last split from the last one, and are not folded (a weight
+  // of 0 would make an infinite output NaN). The reference starts below every
   // score but finite, so that an empty split (m = -inf) weighs 0.
   constexpr int BATCH = 4;
   float M = -3.0e38f, L = 0.0f;
@@ -1296,7 +1297,7 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
       for (int k = 0; k < BATCH; ++k) {
         const size_t pr = min(s0 + k * GROUPS, n_splits - 1) * stride + row;
         ms[k] = p.ws_m[pr];
-        ls[k] = s0 + k * GROUPS < n_splits ? p.ws_l[pr] : 0.0f;
+        ls[k] = p.ws_l[pr];
         load_partial8(static_cast<const T*>(p.ws_o) + pr * kD + d0, v[k]);
       }
       float Mn = M;
@@ -1309,6 +1310,7 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
       for (int i = 0; i < 8; ++i) acc[i] *= a;
 #pragma unroll
       for (int k = 0; k < BATCH; ++k) {
+        if (s0 + k * GROUPS >= n_splits) break;
         const float w = __builtin_amdgcn_exp2f(ms[k] - Mn) * ls[k];
         L += w;
 #pragma unroll
