@@ -642,6 +642,9 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
   bal_seek<T>(p, sh, batch, b, uni(quick_div(lo - uni(sh.pref[b]), start + rq.work)), sh.piece[0], lane);
 }
 
+// One key row of zeros.
+__device__ const uint4 bal_zero_row[kD / 4] = {};
+
 // Key tiles [t0, t1) of the piece's stream, page ids of the context ones
 // staged from tile t0 on.
 template <typename T>
@@ -668,8 +671,9 @@ __device__ __forceinline__ void bal_run(const Params& p, BalShared<T>& sh, const
   // byte offset of the KV head's part of a page
   auto page_of = [&](int id) { return (size_t)(uint32_t)(clampi(id, 0, p.num_pages - 1) * p.hkv + pc.h) << PAGE_SHIFT; };
 
-  // Queue tile j. Rows past the valid keys are read from the tile's first row
-  // (their scores are masked, so they only need to be finite).
+  // Queue tile j. Rows past the valid keys take K from the tile's first row
+  // (their scores are masked) and zeros for V: their probabilities are 0, and
+  // 0 * inf would make a row NaN that is infinite where the first key's V is.
   auto copy = [&](int j, uint32_t dst) {          // dst: byte offset of its slot
     if (j < n_full) {
 #pragma unroll
@@ -693,8 +697,10 @@ __device__ __forceinline__ void bal_run(const Params& p, BalShared<T>& sh, const
     for (int c = 0; c < BT::COPIES; ++c) {
       dma16(src(kc, static_cast<const char*>(p.k_tree), CP::krow(cw, lane) + 16 * c) + CP::kcol(cw, lane),
             dst + kdst + c * CP::K2);
-      dma16(src(vc, static_cast<const char*>(p.v_tree), CP::vrow(cw, lane) + 16 * c) + CP::vcol(cw, lane),
-            dst + vdst + c * CP::V2);
+      const int vr = CP::vrow(cw, lane) + 16 * c;
+      const char* v = src(vc, static_cast<const char*>(p.v_tree), vr);
+      if (vr >= nvalid) v = reinterpret_cast<const char*>(bal_zero_row);
+      dma16(v + CP::vcol(cw, lane), dst + vdst + c * CP::V2);
     }
   };
 

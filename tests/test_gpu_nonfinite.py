@@ -41,3 +41,12 @@ def test_infinite_value_in_the_last_split(kv_split, dtype):
     ctx = [1000, 650, 520, 330]
     lay = wl.custom_layout(16, [[3, 7], [1], [], [2, 5, 9, 15]], ctx, hq=8, hkv=2, dtype=dtype, seed=11)
     check(lay, {b: c - 1 for b, c in enumerate(ctx)}, kv_split=kv_split)
+
+
+# the even division: keys of a partial last tile, of which the first also fills the copy's rows past the valid ones
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("at", ["first of the last tile", "last"])
+def test_infinite_value_beside_padded_keys(at, dtype):
+    ctx = [3000, 1001, 2060, 331, 33]
+    lay = wl.custom_layout(16, [[3, 7], [1], [], [2, 5, 9, 15], [4]], ctx, hq=8, hkv=2, dtype=dtype, seed=12)
+    check(lay, {b: c - 1 if at == "last" else (c - 1) // 32 * 32 for b, c in enumerate(ctx)})
