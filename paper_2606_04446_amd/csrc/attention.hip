@@ -1381,9 +1381,10 @@ hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& pla
                                     hipStream_t stream, hipEvent_t (&ev)[3]) {
   const Params p = make_params(a, plan, ws);
   const int grid = (int)(((plan.items + 7) / 8) * 8);
+  hipError_t e = hipSuccess;
   if (ev[0]) (void)hipEventRecord(ev[0], stream);
   if (plan.workgroups > 0) {
-    (void)launch_balanced_attention(a, plan, ws, stream);
+    e = launch_balanced_attention(a, plan, ws, stream);   // its error is taken here: asking for it clears it
   } else if (a.dtype == D2SD_BF16 && plan.packed) {
     const long long wgs = (plan.tiles + pk::WAVES - 1) / pk::WAVES;
     const int pgrid = (int)(((wgs + 7) / 8) * 8);
@@ -1394,8 +1395,8 @@ hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& pla
     hipLaunchKernelGGL(cascade_bf16_kernel, dim3(grid), dim3(bf::Shape<kBf16Waves>::THREADS), 0, stream, p);
   else
     hipLaunchKernelGGL(cascade_attention_kernel<float>, dim3(grid), dim3(kThreads), 0, stream, p);
+  if (e == hipSuccess) e = hipGetLastError();
   if (ev[1]) (void)hipEventRecord(ev[1], stream);
-  hipError_t e = hipGetLastError();
   if (e == hipSuccess && plan.n_ch_max > 1) {
     const int groups = plan.merge_groups;
     const long long chunks = merge_chunks_per_request(a.max_nodes, a.num_qo_heads, groups);
