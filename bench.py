@@ -421,9 +421,8 @@ def main():
     ws_bytes = d2sd.cascade_workspace_size(a)
     kv_split = d2sd.cascade_kv_split(a)
     row_group, packed = d2sd.cascade_shape(a)
-    # the even division keeps a count per stream beside the partial states, the fixed splits do not
-    balanced = ws_bytes % (total * spec.hq * (spec.head_dim * (2 if spec.dtype == "bf16" else 4) + 8)) != 0
-    n_splits = -(-max_ctx // kv_split) if max_ctx > 0 else 1
+    # most parts a row's keys are taken in: fixed splits, or pieces of the even division
+    balanced, n_splits = d2sd.cascade_division(a)
     ws = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=dev)
     acc = d2sd.accept_path(B, d_ip, total, tree["parent"], tree["depth"], tree["path_id"], d_draft, d_argmax)
 

@@ -301,6 +301,16 @@ d2sd_status d2sd_cascade_kv_split(const d2sd_attn_args* args, int* kv_split);
 d2sd_status d2sd_cascade_row_group(const d2sd_attn_args* args, int* rows, int* packed);
 
 /*
+ * Host. How the attention call will divide the keys of `args`: *even = 1 when
+ * the automatic plan gives every CU an equal share of the batch's key tiles
+ * (see d2sd_cascade_verify_attention), 0 for fixed splits; *parts (nullable)
+ * the most parts the keys of one row are taken in: the splits of the longest
+ * context, or the pieces of a stream. With more than one part the call writes
+ * partial states to the workspace and merges them.
+ */
+d2sd_status d2sd_cascade_division(const d2sd_attn_args* args, int* even, int* parts);
+
+/*
  * Device. Verify attention (see d2sd_attn_args). The M = N_b * G query rows
  * of a (request, KV head) are cut into row groups of 128 or 384 (bf16,
  * d2sd_cascade_row_group), or, in the packed shape, into the 32-row tiles of

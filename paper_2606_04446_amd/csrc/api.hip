@@ -607,6 +607,17 @@ d2sd_status d2sd_cascade_row_group(const d2sd_attn_args* args, int* rows, int* p
   return ok();
 }
 
+d2sd_status d2sd_cascade_division(const d2sd_attn_args* args, int* even, int* parts) {
+  d2sd_status s = validate_attn(args, false);
+  if (s) return s;
+  if (!even) return fail(D2SD_ERR_INVALID_ARG, "even is NULL");
+  d2sd::AttnPlan plan;
+  if ((s = make_plan(args, &plan))) return s;
+  *even = plan.workgroups > 0 ? 1 : 0;
+  if (parts) *parts = plan.n_ch_max;
+  return ok();
+}
+
 d2sd_status d2sd_cascade_workspace_size(const d2sd_attn_args* args, size_t* bytes) {
   d2sd_status s = validate_attn(args, false);
   if (s) return s;

@@ -86,6 +86,7 @@ _commit = _sig("d2sd_commit_accepted_kv", _c_int, _c_int, _c_int, _c_int, _c_int
 _ws_size = _sig("d2sd_cascade_workspace_size", _c_int, ctypes.POINTER(AttnArgs), ctypes.POINTER(_c_size))
 _kv_split = _sig("d2sd_cascade_kv_split", _c_int, ctypes.POINTER(AttnArgs), _c_int_p)
 _row_group = _sig("d2sd_cascade_row_group", _c_int, ctypes.POINTER(AttnArgs), _c_int_p, _c_int_p)
+_division = _sig("d2sd_cascade_division", _c_int, ctypes.POINTER(AttnArgs), _c_int_p, _c_int_p)
 _cascade = _sig("d2sd_cascade_verify_attention", _c_int, ctypes.POINTER(AttnArgs), _c_ptr, _c_size, _c_ptr)
 _noncascade = _sig("d2sd_noncascade_verify_attention", _c_int, ctypes.POINTER(AttnArgs), _c_ptr)
 _cascade_noalloc = _sig("d2sd_cascade_verify_attention_noalloc", _c_int, ctypes.POINTER(AttnArgs), _c_ptr)
@@ -313,6 +314,14 @@ def cascade_shape(args: AttnArgs) -> tuple:
     pk = ctypes.c_int(0)
     _check(_row_group(ctypes.byref(args), ctypes.byref(n), ctypes.byref(pk)), "d2sd_cascade_row_group")
     return n.value, bool(pk.value)
+
+
+def cascade_division(args: AttnArgs) -> tuple:
+    """(even division, most parts the keys of a row are taken in) of the call's plan."""
+    even = ctypes.c_int(0)
+    parts = ctypes.c_int(0)
+    _check(_division(ctypes.byref(args), ctypes.byref(even), ctypes.byref(parts)), "d2sd_cascade_division")
+    return bool(even.value), parts.value
 
 
 def cascade_kv_split(args: AttnArgs) -> int:

@@ -393,6 +393,27 @@ def test_automatic_split():
     assert s2 % 64 == 0 and s2 >= 256 and math.ceil(4096 / s2) > 1
 
 
+EIGHT = dict(batch=8, total_nodes=384, max_nodes=48, max_ctx_len=8192, max_pages=512, num_pages=4096)
+
+
+def test_division_of_the_keys():
+    """The plan tells how it divides the keys: fixed splits and their number,
+    or the even division, which always has partial states."""
+    assert d2sd.cascade_division(good_args(kv_split=16384)) == (False, 1)
+    assert d2sd.cascade_division(good_args(kv_split=4096)) == (False, 4)
+    assert d2sd.cascade_division(good_args(stage=d2sd.STAGE_TREE, kv_split=64)) == (False, 1)
+    for dtype in (d2sd.BF16, d2sd.F32):
+        a = good_args(dtype=dtype, **EIGHT)
+        even, parts = d2sd.cascade_division(a)
+        assert even and 2 <= parts <= 256 and ws_size(a)[1] > 0
+        a.row_group = 128                          # an explicit choice: fixed splits
+        assert not d2sd.cascade_division(a)[0]
+    n = ctypes.c_int(7)
+    assert d2sd._division(ctypes.byref(good_args()), None, ctypes.byref(n)) == d2sd.ERR_INVALID_ARG
+    assert d2sd._division(ctypes.byref(good_args()), ctypes.byref(n), None) == d2sd.OK
+    assert d2sd._division(ctypes.byref(good_args(batch=0)), ctypes.byref(n), None) == d2sd.ERR_INVALID_ARG
+
+
 def test_noncascade_validation():
     a = good_args(stage=d2sd.STAGE_PREFIX)
     assert d2sd._noncascade(ctypes.byref(a), None) == d2sd.ERR_INVALID_ARG

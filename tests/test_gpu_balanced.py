@@ -2,8 +2,7 @@
 that the automatic plan takes there, at the sizes where it can go wrong.
 
 The plan is the automatic one (no split, row group or packing asked for), so
-each case first checks that the partial-state size is the even division's (it
-has a count per stream, which the fixed splits do not)."""
+each case first checks that it is the even division."""
 
 import numpy as np
 import pytest
@@ -15,10 +14,14 @@ from tests.gpu_cases import Case, TOL, d2sd, max_abs
 pytestmark = pytest.mark.gpu
 
 
+def even_case(lay, host_offsets=True, **kw):
+    case = Case(lay, **kw)
+    assert d2sd().cascade_division(case._args(host_offsets=host_offsets))[0], "not the even division"
+    return case
+
+
 def check(lay, stages=(0,), host_offsets=True, reqs=None):
-    case = Case(lay, poison_slack=True)
-    rows = case.total * lay.spec.hq * (128 * (2 if case.dtype == "bf16" else 4) + 8)
-    assert d2sd().cascade_workspace_size(case._args(host_offsets=host_offsets)) % rows != 0, "not the even division"
+    case = even_case(lay, host_offsets, poison_slack=True)
     for stage in stages:
         o, l = case.attention(stage=stage, host_offsets=host_offsets)
         torch.cuda.synchronize()
@@ -74,7 +77,7 @@ def test_page_list_longer_than_one_staging():
     lay = wl.custom_layout(8, [[]] * 16, [40000] * 16, hq=16, hkv=16, seed=3)
     lay.page_table = np.random.default_rng(3).integers(0, 500, lay.page_table.shape).astype(np.int32)
     lay.num_pages = 500
-    case = Case(lay)
+    case = even_case(lay)
     o, l = case.attention(host_offsets=True)
     torch.cuda.synchronize()
     for b in (0, 15):
@@ -88,7 +91,7 @@ def test_large_scores(scale):
     """Scores far above the first tile's reference: the reference moves in the
     middle of a stream, by more than the exponent range at the larger scale."""
     lay = wl.custom_layout(16, [[3, 9], [1]], [1500, 1100], hq=8, hkv=2, seed=11)
-    case = Case(lay)
+    case = even_case(lay)
     case.x["q"].mul_(scale)
     o, l = case.attention(host_offsets=True)
     torch.cuda.synchronize()
@@ -104,7 +107,7 @@ def test_large_scores(scale):
 def test_two_streams_with_their_own_workspaces():
     """Two calls in flight on two streams give what each gives alone."""
     lays = [wl.custom_layout(16, [[3, 9], [1]], [3000, 1100], hq=8, hkv=2, seed=s) for s in (21, 22)]
-    cases = [Case(x) for x in lays]
+    cases = [even_case(x) for x in lays]
     alone = [c.attention(host_offsets=True) for c in cases]
     torch.cuda.synchronize()
     streams = [torch.cuda.Stream() for _ in cases]
