@@ -288,7 +288,10 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
 //    1176 -> 1129). With fewer tiles the four-wave shape is as fast (64 of
 //    8000, 2-3 tiles: 391 -> 398), with more the 384-row shapes are faster
 //    (32 of 16k, 9-11 tiles: 837 -> 857; 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms).
+// Never without context keys (the tree stage is one launch and needs no
+// workspace) and never for an empty batch.
 bool balanced_pays(const d2sd_attn_args* a, int G, bool large_grid) {
+  if (a->stage == D2SD_STAGE_TREE || a->total_nodes == 0) return false;
   if (a->dtype == D2SD_F32) return a->max_ctx_len > kMinSplitF32;
   if (a->max_ctx_len < 1000) return false;
   const long long tiles = ((long long)a->max_nodes * G + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile;

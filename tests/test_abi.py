@@ -414,6 +414,15 @@ def test_division_of_the_keys():
     assert d2sd._division(ctypes.byref(good_args(batch=0)), ctypes.byref(n), None) == d2sd.ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("dtype", [d2sd.BF16, d2sd.F32])
+def test_calls_without_context_keys_or_rows_need_no_workspace(dtype):
+    a = good_args(dtype=dtype, stage=d2sd.STAGE_TREE, **EIGHT)
+    assert d2sd.cascade_division(a) == (False, 1) and ws_size(a) == (d2sd.OK, 0)
+    a = good_args(dtype=dtype, **{**EIGHT, "total_nodes": 0, "max_nodes": 0})
+    assert not d2sd.cascade_division(a)[0] and ws_size(a) == (d2sd.OK, 0)
+    assert d2sd._cascade(ctypes.byref(a), None, 0, None) == d2sd.OK       # nothing to launch
+
+
 def test_noncascade_validation():
     a = good_args(stage=d2sd.STAGE_PREFIX)
     assert d2sd._noncascade(ctypes.byref(a), None) == d2sd.ERR_INVALID_ARG
