@@ -282,20 +282,18 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
 //    on (8 requests of 1k-8k: 90 -> 69; 1 of 32k: 74 -> 50; 1 of 1000:
 //    24 -> 23). Below, the second launch costs more than the division gives
 //    (4 of 600-800: 25 -> 28; 16 of 300-500: 23 -> 38).
-//  - bf16, larger grids: with five to eight query tiles per stream, where a
-//    384-row workgroup idles a third of its waves and the four-wave shape
-//    reads the context twice (32 requests of 4k-16k: 485 -> 404; 64 of 16k:
-//    1176 -> 1129). With fewer tiles the four-wave shape is as fast (64 of
-//    8000, 2-3 tiles: 391 -> 398), with more the 384-row shapes are faster
-//    (32 of 16k, 9-11 tiles: 837 -> 857; 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms).
+//  - bf16, larger grids: not at all. One split fills the chip there, and every
+//    row goes from registers to the output. With five to eight query tiles per
+//    stream: 64 requests of 1k 94 -> 118; 64 of 2k-8k 365 -> 375; 48 of 16k
+//    909 -> 936; 96 of 16k 1824 -> 1848; 192 of 4k 977 -> 994 (64 of 16k
+//    1189 -> 1129); with fewer 64 of 8000: 391 -> 398; with more 32 of 16k:
+//    837 -> 857, 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms.
 // Never without context keys (the tree stage is one launch and needs no
 // workspace) and never for an empty batch.
-bool balanced_pays(const d2sd_attn_args* a, int G, bool large_grid) {
+bool balanced_pays(const d2sd_attn_args* a, bool large_grid) {
   if (a->stage == D2SD_STAGE_TREE || a->total_nodes == 0) return false;
   if (a->dtype == D2SD_F32) return a->max_ctx_len > kMinSplitF32;
-  if (a->max_ctx_len < 1000) return false;
-  const long long tiles = ((long long)a->max_nodes * G + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile;
-  return !large_grid || (tiles > 4 && tiles <= 8);
+  return !large_grid && a->max_ctx_len >= 1000;
 }
 
 // Most pieces a stream of the balanced shape is cut into: four times an equal
@@ -393,7 +391,7 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
     const int s = (int)((2 * R4 + g4 - 1) / g4);
     sh.splits = max(s_lo, min(s, s_hi));
   }
-  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, G, g4 * s_lo >= R4))
+  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4))
     plan->workgroups = balanced_workgroups(a, G);
   if (plan->workgroups > 0) sh = Shape{d2sd::kBf16Waves, false, sh.splits};
   plan->waves = sh.waves;

@@ -423,6 +423,16 @@ def test_calls_without_context_keys_or_rows_need_no_workspace(dtype):
     assert d2sd._cascade(ctypes.byref(a), None, 0, None) == d2sd.OK       # nothing to launch
 
 
+@pytest.mark.parametrize("batch,ctx,nodes", [(64, 1024, 44), (48, 16384, 60), (96, 16384, 60), (192, 4096, 64)])
+def test_bf16_grids_that_fill_the_chip_keep_whole_streams(batch, ctx, nodes):
+    """Streams of five to eight query tiles that fill the chip with one split:
+    no stream is cut, and no workspace is needed."""
+    ip = np.arange(batch + 1, dtype=np.int32) * nodes
+    a = _with_host_indptr(good_args(batch=batch, total_nodes=batch * nodes, max_nodes=nodes, max_ctx_len=ctx,
+                                    max_pages=1024, num_pages=batch * 1024), ip)
+    assert d2sd.cascade_division(a) == (False, 1) and ws_size(a) == (d2sd.OK, 0)
+
+
 def test_noncascade_validation():
     a = good_args(stage=d2sd.STAGE_PREFIX)
     assert d2sd._noncascade(ctypes.byref(a), None) == d2sd.ERR_INVALID_ARG
