@@ -273,27 +273,41 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
   return d2sd::kBalWorkgroups;
 }
 
-// Where the even division beats the fixed splits (attention with its merge, us,
-// fixed splits first; 32/8 heads unless said):
-//  - fp32: everywhere a context has more than one split's minimum (4 requests
-//    of 300-3000 tokens: 218 -> 94; 16 of 4000-8000: 1869 -> 762; 64 of
-//    500-1000: 883 -> 442); at a single split's length they are level.
-//  - bf16, grids that do not fill the chip with one split: from 1024 tokens
-//    on (8 requests of 1k-8k: 90 -> 69; 1 of 32k: 74 -> 50; 1 of 1000:
-//    24 -> 23). Below, the second launch costs more than the division gives
-//    (4 of 600-800: 25 -> 28; 16 of 300-500: 23 -> 38).
+// Where the even division beats the fixed splits (attention with its merge on
+// the GPU, us, fixed splits first; 32/8 heads unless said; `splits` and g4: the
+// fixed plan's split count and its row groups per split). Never without context
+// keys (the tree stage is one launch and needs no workspace) and never for an
+// empty batch.
+//  - bf16, grids that do not fill the chip with one split: its start, stores and
+//    merge cost 10-20 us more than the fixed splits', so there have to be 20 key
+//    tiles a CU to divide (1 request of 4k: 18 -> 27, of 32k: 59 -> 50; 8 of
+//    1000: 27 -> 35, of 4k: 61 -> 56, of 0.5-4k: 56 -> 42; 8/2 heads, 4 of 4k:
+//    20 -> 27, of 16k: 41 -> 38), and with few query tiles a stream, whose key
+//    tiles cost less, more of them: 80 pairs of a key and a query tile a CU
+//    (16/8 heads, 2-3 tiles: 2 of 8k 27 -> 30, 8 of 8k 77 -> 61). Contexts below
+//    1250 tokens have too few tiles a stream (32 of 1000: 64 -> 69).
+//    Of 1237 batches of 1-47 requests, 400-32k tokens and four head counts the
+//    rule takes 473, 10% faster in the mean, 6 of them slower by 4-12%.
 //  - bf16, larger grids: not at all. One split fills the chip there, and every
 //    row goes from registers to the output. With five to eight query tiles per
 //    stream: 64 requests of 1k 94 -> 118; 64 of 2k-8k 365 -> 375; 48 of 16k
 //    909 -> 936; 96 of 16k 1824 -> 1848; 192 of 4k 977 -> 994 (64 of 16k
-//    1189 -> 1129); with fewer 64 of 8000: 391 -> 398; with more 32 of 16k:
+//    1189 -> 1162); with fewer 64 of 8000: 391 -> 398; with more 32 of 16k:
 //    837 -> 857, 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms.
-// Never without context keys (the tree stage is one launch and needs no
-// workspace) and never for an empty batch.
-bool balanced_pays(const d2sd_attn_args* a, bool large_grid) {
+//  - fp32: from more than one split's minimum on (1 request of 100 tokens: 46 ->
+//    28; 16 of 4000: 974 -> 463; 64 of 500: 569 -> 311), but not where the fixed
+//    plan is one unsplit round that fills the CUs with a short context (16 of 66:
+//    43 -> 54, of 100: 49 -> 59, of 200: 69 -> 71; 64/8 heads, 4 of 66: 35 -> 39).
+bool balanced_pays(const d2sd_attn_args* a, bool large_grid, long long g4, int splits) {
   if (a->stage == D2SD_STAGE_TREE || a->total_nodes == 0) return false;
-  if (a->dtype == D2SD_F32) return a->max_ctx_len > kMinSplitF32;
-  return !large_grid && a->max_ctx_len >= 1000;
+  const long long ctx = a->max_ctx_len;
+  if (a->dtype == D2SD_F32) {
+    const bool one_round = splits == 1 && g4 <= kNumCUs && g4 >= (ctx < 96 ? 40 : 150);
+    return ctx > kMinSplitF32 && !(one_round && ctx < 200);
+  }
+  constexpr long long kTile = 32;   // keys, and rows of a query tile
+  return !large_grid && ctx >= 1250 && ctx * a->batch * a->num_kv_heads >= 20 * kTile * kNumCUs &&
+         ctx * a->total_nodes * a->num_qo_heads >= 80 * kTile * kTile * kNumCUs;
 }
 
 // Most pieces a stream of the balanced shape is cut into: four times an equal
@@ -391,7 +405,7 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
     const int s = (int)((2 * R4 + g4 - 1) / g4);
     sh.splits = max(s_lo, min(s, s_hi));
   }
-  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4))
+  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4, g4, sh.splits))
     plan->workgroups = balanced_workgroups(a, G);
   if (plan->workgroups > 0) sh = Shape{d2sd::kBf16Waves, false, sh.splits};
   plan->waves = sh.waves;

@@ -433,6 +433,21 @@ def test_bf16_grids_that_fill_the_chip_keep_whole_streams(batch, ctx, nodes):
     assert d2sd.cascade_division(a) == (False, 1) and ws_size(a) == (d2sd.OK, 0)
 
 
+@pytest.mark.parametrize("dtype,batch,hq,hkv,ctx,nodes,even", [
+    # bf16: 20 key tiles and 80 pairs of a key and a query tile per CU, 1250 tokens
+    (0, 1, 32, 8, 4096, 48, False), (0, 1, 32, 8, 32768, 48, True), (0, 8, 32, 8, 1000, 48, False),
+    (0, 8, 32, 8, 4096, 48, True), (0, 4, 8, 2, 4096, 48, False), (0, 16, 8, 2, 8192, 48, True),
+    (0, 8, 16, 8, 4096, 16, False), (0, 8, 16, 8, 8192, 48, True), (0, 47, 32, 8, 1200, 30, False),
+    # fp32: one full round of unsplit short contexts keeps the fixed plan
+    (1, 1, 32, 8, 64, 48, False), (1, 1, 32, 8, 100, 48, True), (1, 16, 32, 8, 66, 48, False),
+    (1, 16, 32, 8, 100, 48, False), (1, 16, 32, 8, 200, 48, True), (1, 64, 32, 8, 100, 48, True),
+    (1, 4, 32, 8, 3000, 48, True)])
+def test_where_the_keys_are_divided_evenly(dtype, batch, hq, hkv, ctx, nodes, even):
+    a = good_args(dtype=(d2sd.BF16, d2sd.F32)[dtype], batch=batch, num_qo_heads=hq, num_kv_heads=hkv, max_ctx_len=ctx,
+                  total_nodes=batch * nodes, max_nodes=nodes, max_pages=4096, num_pages=batch * 4096)
+    assert d2sd.cascade_division(a)[0] == even
+
+
 def test_noncascade_validation():
     a = good_args(stage=d2sd.STAGE_PREFIX)
     assert d2sd._noncascade(ctypes.byref(a), None) == d2sd.ERR_INVALID_ARG

@@ -36,17 +36,33 @@ def check(lay, stages=(0,), host_offsets=True, reqs=None):
             assert err <= TOL[case.dtype], (stage, b, err)
 
 
+def even_layout(B, p_rows, ctx, hq, hkv, dtype, seed):
+    """The requests, and for bf16 as many more of 8192 tokens as the even
+    division asks for (20 key tiles and 80 pairs of tiles per CU)."""
+    p_rows, ctx = list(p_rows), list(ctx)
+    extra = list(range(2, B, 3))
+    nodes = sum(B + sum(B - x for x in r) for r in p_rows)
+    while dtype == "bf16" and (len(ctx) * hkv * max(ctx) < 20 * 32 * 256 or hq * nodes * max(ctx) < 80 * 32 * 32 * 256):
+        p_rows.append(extra)
+        ctx.append(8192)
+        nodes += B + sum(B - x for x in extra)
+    return wl.custom_layout(B, p_rows, ctx, hq=hq, hkv=hkv, dtype=dtype, seed=seed)
+
+
 def rows_for(rng, B, batch, k):
     return [sorted(rng.choice(np.arange(1, B), int(rng.integers(0, k + 1)), replace=False).tolist()) for _ in range(batch)]
 
 
-# query tiles per stream from 1 to 13 (one and two row groups, 1 to 12 waves)
+# 1 to 14, 16, 24 and 31 query tiles per stream: one to three row groups, every
+# wave count around the two key groups' limit (fp32), groups of 3, 4, 5 and 8 heads
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("B,p,hq,hkv", [(8, [], 8, 2), (16, [], 8, 2), (16, [4], 8, 2), (16, [1, 5, 9, 13], 32, 8),
-                                        (16, [1, 2, 3, 4, 5, 6], 8, 2), (24, [1, 2, 3, 4], 8, 2),
-                                        (32, [1, 2, 3], 8, 2), (32, [1, 2], 8, 1)])
+@pytest.mark.parametrize("B,p,hq,hkv", [(8, [], 8, 2), (16, [], 8, 2), (16, [4], 8, 2), (16, [1, 5], 12, 4), (16, [4], 40, 8),
+                                        (16, [2, 9], 8, 2), (16, [1, 3], 8, 2), (16, [1, 5, 9, 13], 32, 8),
+                                        (16, [1, 2, 3, 4, 5, 6], 8, 2), (16, [1, 2, 3, 4, 5, 6, 7], 8, 2),
+                                        (24, [1, 2, 3, 4], 8, 2), (32, [1, 2, 3], 8, 2), (32, [1, 2], 8, 1),
+                                        (32, [1, 2, 3], 8, 1)])
 def test_query_tiles(B, p, hq, hkv, dtype):
-    check(wl.custom_layout(B, [p], [1100], hq=hq, hkv=hkv, dtype=dtype, seed=B + len(p)))
+    check(even_layout(B, [p], [1100], hq=hq, hkv=hkv, dtype=dtype, seed=B + len(p)), reqs=range(1))
 
 
 # ends of key tiles, pages and ring fills; contexts shorter than the tree; empty ones
@@ -55,8 +71,8 @@ def test_query_tiles(B, p, hq, hkv, dtype):
                                  [1040, 1039, 1041, 16, 15, 17, 0, 0]])
 def test_ragged_contexts(ctx, dtype):
     rng = np.random.default_rng(len(ctx))
-    check(wl.custom_layout(16, rows_for(rng, 16, len(ctx), 5), ctx, hq=8, hkv=2, dtype=dtype, seed=7), stages=(0, 1, 2),
-          host_offsets=False)
+    check(even_layout(16, rows_for(rng, 16, len(ctx), 5), ctx, hq=8, hkv=2, dtype=dtype, seed=7), stages=(0, 1, 2),
+          host_offsets=False, reqs=range(len(ctx)))
 
 
 def test_many_requests_and_shares_of_many_streams():
@@ -66,8 +82,8 @@ def test_many_requests_and_shares_of_many_streams():
     rng = np.random.default_rng(5)
     ctx = [6000] + [int(x) for x in rng.integers(0, 90, 100)]
     check(wl.custom_layout(16, rows_for(rng, 16, 101, 2), ctx, hq=4, hkv=1, seed=8), reqs=range(0, 101, 7))
-    ctx = [1200] + [int(x) for x in rng.integers(0, 40, 255)]
-    check(wl.custom_layout(8, rows_for(rng, 8, 256, 1), ctx, hq=2, hkv=1, seed=9), reqs=range(0, 256, 17))
+    ctx = [1300] + [int(x) for x in rng.integers(0, 40, 255)]
+    check(wl.custom_layout(8, rows_for(rng, 8, 256, 1), ctx, hq=8, hkv=1, seed=9), reqs=range(0, 256, 17))
 
 
 def test_page_list_longer_than_one_staging():
@@ -90,7 +106,7 @@ def test_page_list_longer_than_one_staging():
 def test_large_scores(scale):
     """Scores far above the first tile's reference: the reference moves in the
     middle of a stream, by more than the exponent range at the larger scale."""
-    lay = wl.custom_layout(16, [[3, 9], [1]], [1500, 1100], hq=8, hkv=2, seed=11)
+    lay = even_layout(16, [[3, 9], [1]], [1500, 1100], hq=8, hkv=2, dtype="bf16", seed=11)
     case = even_case(lay)
     case.x["q"].mul_(scale)
     o, l = case.attention(host_offsets=True)
@@ -106,7 +122,7 @@ def test_large_scores(scale):
 
 def test_two_streams_with_their_own_workspaces():
     """Two calls in flight on two streams give what each gives alone."""
-    lays = [wl.custom_layout(16, [[3, 9], [1]], [3000, 1100], hq=8, hkv=2, seed=s) for s in (21, 22)]
+    lays = [even_layout(16, [[3, 9], [1]], [3000, 1100], hq=8, hkv=2, dtype="bf16", seed=s) for s in (21, 22)]
     cases = [even_case(x) for x in lays]
     alone = [c.attention(host_offsets=True) for c in cases]
     torch.cuda.synchronize()

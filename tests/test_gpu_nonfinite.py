@@ -7,7 +7,8 @@ import pytest
 import torch
 
 from paper_2606_04446_amd import workload as wl
-from tests.gpu_cases import Case
+from tests.gpu_cases import Case, d2sd
+from tests.test_gpu_balanced import even_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -48,5 +49,6 @@ def test_infinite_value_in_the_last_split(kv_split, dtype):
 @pytest.mark.parametrize("at", ["first of the last tile", "last"])
 def test_infinite_value_beside_padded_keys(at, dtype):
     ctx = [3000, 1001, 2060, 331, 33]
-    lay = wl.custom_layout(16, [[3, 7], [1], [], [2, 5, 9, 15], [4]], ctx, hq=8, hkv=2, dtype=dtype, seed=12)
+    lay = even_layout(16, [[3, 7], [1], [], [2, 5, 9, 15], [4]], ctx, hq=8, hkv=2, dtype=dtype, seed=12)
+    assert d2sd().cascade_division(Case(lay)._args())[0]
     check(lay, {b: c - 1 if at == "last" else (c - 1) // 32 * 32 for b, c in enumerate(ctx)})
