@@ -270,14 +270,13 @@ __device__ __forceinline__ int bal_vaddr<float>(int lane) {
 constexpr float kNoReference = -3.0e38f;
 
 // Moves the exponent reference of a query row (m, in log2 units) when the
-// tile's largest score exceeds it by more than `slack`, rescaling O and l. The
-// reference is a whole number, so a probability 2^(score c2 - m) rounds to the
-// same bf16 mantissa whatever the reference, and rescaling is exact: where a
-// stream is cut does not change how its probabilities are rounded.
+// tile's largest score exceeds it by more than `slack`, rescaling O and l. It is
+// the score itself, so that the largest probability is exactly 1 in bf16 (as a
+// whole number above it, it left a row's dominant key with a rounding error).
 __device__ __forceinline__ void bal_reference(float mx, float slack, float c2, float& m, float& l, f32x16 (&o)[4]) {
   const float top = xhalf_max(mx) * c2;
   if (__ballot(top - m > slack)) {
-    const float m_new = fmaxf(m, ceilf(top));
+    const float m_new = fmaxf(m, top);
     const float alpha = __builtin_amdgcn_exp2f(m - m_new);
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;

@@ -120,6 +120,26 @@ def test_large_scores(scale):
         assert max_abs(l[s:e].cpu().numpy(), lw) <= tol
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_dominant_first_key_has_weight_one(dtype):
+    """A key of the first tile that holds nearly all the weight of every row has
+    probability 1, which bf16 holds exactly: lse is its score to the accuracy of
+    fp32 sums (1e-6 of a score of about 28), not of a bf16 probability (2e-3)."""
+    case = even_case(even_layout(16, [[3, 9], [1], []], [1500, 1100, 700], hq=8, hkv=2, dtype=dtype, seed=13))
+    u = torch.zeros(128, device="cuda")
+    u[::2] = 0.125                                             # a unit vector, exact in bf16
+    case.x["q"] += 8 * u
+    for b in range(3):
+        case.x["k_cache"][int(case.layout.page_table[b, 0]), :, 3] = 40 * u
+    o, l = case.attention(host_offsets=True)
+    torch.cuda.synchronize()
+    for b in range(3):
+        s, e = int(case.node_indptr[b]), int(case.node_indptr[b + 1])
+        ow, lw = case.oracle_attention(b)
+        assert max_abs(l[s:e].cpu().numpy(), lw) <= 1e-4
+        assert max_abs(o[s:e].double().cpu().numpy(), ow) <= TOL[dtype]
+
+
 def test_two_streams_with_their_own_workspaces():
     """Two calls in flight on two streams give what each gives alone."""
     lays = [even_layout(16, [[3, 9], [1]], [3000, 1100], hq=8, hkv=2, dtype="bf16", seed=s) for s in (21, 22)]
