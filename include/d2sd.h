@@ -278,7 +278,10 @@ typedef struct d2sd_attn_args {
 /*
  * Host. Device workspace bytes d2sd_cascade_verify_attention needs for `args`
  * (partial states of the context splits). Writes *bytes (0 when no split is
- * needed). Errors: INVALID_ARG / UNSUPPORTED as the attention call would.
+ * needed). The even division (see d2sd_cascade_division) always needs some: two
+ * slots of a stream's rows per CU at most (256 and one per stream, up to 512),
+ * 520 bytes a row, of at most 384 rows: 4 to 102 MB whatever the contexts are.
+ * Errors: INVALID_ARG / UNSUPPORTED as the attention call would.
  */
 d2sd_status d2sd_cascade_workspace_size(const d2sd_attn_args* args, size_t* bytes);
 
@@ -338,10 +341,11 @@ d2sd_status d2sd_cascade_verify_attention(const d2sd_attn_args* args, void* ws, 
  * every GPU the library runs on until the process ends. With an explicit
  * kv_split whose partial states exceed 64 MiB it returns
  * D2SD_ERR_WORKSPACE_TOO_SMALL; with the automatic split (kv_split = 0) it
- * takes the automatic plan, or, when that does not fit, fewer and longer
- * splits that do (the results then differ from the workspace entry
- * point's by summation order only), and returns D2SD_ERR_WORKSPACE_TOO_SMALL
- * if even ceil(max_ctx_len / 32768) splits do not fit. The scratch holds
+ * takes the automatic plan, or, when that does not fit, fixed splits that do,
+ * fewer and longer ones if need be (the results then differ from the workspace
+ * entry point's by summation order and the rounding of partial states only),
+ * and returns D2SD_ERR_WORKSPACE_TOO_SMALL if even ceil(max_ctx_len / 32768)
+ * splits do not fit. The scratch holds
  * nothing that must start at zero; every call on one GPU shares it and
  * leaves its last contents there, so calls that overlap on one GPU (two
  * streams, two host threads) race. Arguments, errors and outputs otherwise

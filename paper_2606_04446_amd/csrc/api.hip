@@ -310,15 +310,10 @@ bool balanced_pays(const d2sd_attn_args* a, bool large_grid, long long g4, int s
          ctx * a->total_nodes * a->num_qo_heads >= 80 * kTile * kTile * kNumCUs;
 }
 
-// Most pieces a stream of the balanced shape is cut into: four times an equal
-// share of the workgroups (contexts up to four times the mean are divided
-// evenly, longer ones less finely), and no more than its key tiles.
-int balanced_pieces(const d2sd_attn_args* a) {
-  const int even = (kNumCUs + a->num_kv_heads - 1) / a->num_kv_heads;      // one request
-  const int wanted = (4 * kNumCUs + a->num_kv_heads * a->batch - 1) / (a->num_kv_heads * a->batch);
-  const int key_tiles = (a->max_ctx_len + 31) / 32 + (a->max_nodes + 31) / 32;
-  return max(2, min(min(even, wanted) + 1, key_tiles));
-}
+// Most pieces a stream of the balanced shape is cut into: a request's streams,
+// one per KV head at least, are equal parts of the line of costs, so each has
+// at most this share of the workgroups (and pieces at both ends).
+int balanced_pieces(const d2sd_attn_args* a) { return kNumCUs / a->num_kv_heads + 2; }
 
 struct Shape {
   int waves;
@@ -346,7 +341,7 @@ constexpr double kPackMargin = 0.97;
 // costs as many bytes as ~M/2 keys of K/V, M = rows sharing it; fp32 splits
 // are compute-bound and can be shorter) or longer than the staged page list
 // allows. An explicit kv_split, row_group or packed fixes that choice.
-void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
+void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan, bool even) {
   plan->workgroups = 0;
   const bool bf16 = a->dtype == D2SD_BF16;
   const int ctx = a->max_ctx_len;
@@ -405,7 +400,7 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
     const int s = (int)((2 * R4 + g4 - 1) / g4);
     sh.splits = max(s_lo, min(s, s_hi));
   }
-  if (a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4, g4, sh.splits))
+  if (even && a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4, g4, sh.splits))
     plan->workgroups = balanced_workgroups(a, G);
   if (plan->workgroups > 0) sh = Shape{d2sd::kBf16Waves, false, sh.splits};
   plan->waves = sh.waves;
@@ -421,20 +416,23 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan) {
   }
 }
 
-// Partial states of one split: per row the normalised output in the input
-// dtype, then m and l in fp32.
-size_t split_bytes(const d2sd_attn_args* a) {
+// Partial states: per row the normalised output, then m and l in fp32. The
+// output is in the input dtype for fixed splits (one state per row and split).
+// In the balanced shape it is fp32, in slots of a row group's rows, and the
+// piece counts of the streams follow.
+size_t split_bytes(const d2sd_attn_args* a, const d2sd::AttnPlan& plan) {
   const size_t rows = (size_t)a->total_nodes * a->num_qo_heads;
-  return rows * (a->head_dim * (a->dtype == D2SD_BF16 ? 2 : 4) + 2 * sizeof(float));
+  return plan.n_ch_max * rows * (a->head_dim * (a->dtype == D2SD_BF16 ? 2 : 4) + 2 * sizeof(float));
 }
-// Balanced shape: the number of pieces of every stream.
-size_t piece_count_bytes(const d2sd_attn_args* a, const d2sd::AttnPlan& plan) {
-  return plan.workgroups > 0 ? (size_t)a->batch * a->num_kv_heads * plan.n_rg_max * sizeof(int) : 0;
+size_t balanced_bytes(const d2sd_attn_args* a, const d2sd::AttnPlan& plan) {
+  const size_t states = (size_t)plan.slots * plan.slot_rows;
+  return states * (a->head_dim + 2) * sizeof(float) + (size_t)a->batch * a->num_kv_heads * plan.n_rg_max * sizeof(int);
 }
 
-d2sd_status make_plan(const d2sd_attn_args* a, d2sd::AttnPlan* plan) {
+// even: whether the automatic plan may be the balanced shape.
+d2sd_status make_plan(const d2sd_attn_args* a, d2sd::AttnPlan* plan, bool even = true) {
   plan->G = a->num_qo_heads / a->num_kv_heads;
-  choose_shape(a, plan->G, plan);
+  choose_shape(a, plan->G, plan, even);
   const bool ctx = a->stage != D2SD_STAGE_TREE;
   plan->n_ch_max = ctx ? max(1, (a->max_ctx_len + plan->split - 1) / plan->split) : 1;
   if (plan->packed) {
@@ -456,7 +454,14 @@ d2sd_status make_plan(const d2sd_attn_args* a, d2sd::AttnPlan* plan) {
           (1ll << 30))
     return fail(D2SD_ERR_UNSUPPORTED, "too many split-merge workgroups (batch %d, max_nodes %d)", a->batch,
                 a->max_nodes);
-  plan->ws_bytes = plan->n_ch_max > 1 ? plan->n_ch_max * split_bytes(a) + piece_count_bytes(a, *plan) : 0;
+  plan->slots = plan->slot_rows = 0;
+  plan->ws_bytes = plan->n_ch_max > 1 ? split_bytes(a, *plan) : 0;
+  if (plan->workgroups > 0) {
+    const long long streams = (long long)a->batch * a->num_kv_heads * plan->n_rg_max;
+    plan->slots = d2sd::kBalWorkgroups + (int)min((long long)d2sd::kBalWorkgroups, streams);
+    plan->slot_rows = (int)min((long long)rows_per_group, (max_rows + d2sd::kRowsPerTile - 1) / d2sd::kRowsPerTile * d2sd::kRowsPerTile);
+    plan->ws_bytes = balanced_bytes(a, *plan);
+  }
   plan->scale = a->sm_scale > 0.0f ? a->sm_scale : 1.0f / sqrtf((float)a->head_dim);
   return D2SD_OK;
 }
@@ -665,15 +670,8 @@ d2sd_status d2sd_cascade_verify_attention_noalloc(const d2sd_attn_args* args, hi
   if (s) return s;
   d2sd::AttnPlan plan;
   if ((s = make_plan(args, &plan))) return s;
-  if (plan.workgroups > 0 && plan.ws_bytes > d2sd::kScratchBytes) {
-    // the same division with fewer, longer pieces per stream
-    const size_t counts = piece_count_bytes(args, plan);
-    const size_t pieces = counts < d2sd::kScratchBytes ? (d2sd::kScratchBytes - counts) / split_bytes(args) : 0;
-    if (pieces >= 2) {
-      plan.n_ch_max = (int)pieces;
-      plan.ws_bytes = pieces * split_bytes(args) + counts;
-    }
-  }
+  // an even division whose partial states do not fit leaves the call to the fixed splits
+  if (plan.workgroups > 0 && plan.ws_bytes > d2sd::kScratchBytes && (s = make_plan(args, &plan, false))) return s;
   if (plan.ws_bytes > d2sd::kScratchBytes) {
     if (args->kv_split > 0)
       return fail(D2SD_ERR_WORKSPACE_TOO_SMALL,

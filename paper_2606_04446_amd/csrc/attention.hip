@@ -1251,7 +1251,8 @@ __device__ __forceinline__ void load_partial8(const __bf16* src, float (&v)[8]) 
   }
 }
 
-template <typename T, int GROUPS>
+// T: the output's type, P: that of the partial outputs.
+template <typename T, typename P, int GROUPS, bool BALANCED>
 __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chunks) {
   constexpr int ROWS = merge_rows(GROUPS);
   static_assert(ROWS * GROUPS * 16 == kThreads, "16 threads per group and row");
@@ -1268,21 +1269,31 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
   // shape, the pieces of the row's stream (quotients of numbers below 2^21 by
   // float reciprocals: integer divisions were most of the kernel's time)
   int n_splits = 0;
-  if (!p.ws_pieces) {
+  const int row = node_base * p.hq + r;
+  size_t at0 = row, at1 = row;             // partial states of split 0, and of split s >= 1 less s strides
+  size_t stride = (size_t)p.total_nodes * p.hq;
+  if constexpr (!BALANCED) {
     n_splits = ceil_div(clampi(p.ctx_len[b], 0, p.max_ctx), p.split);
   } else if (r < Nb * p.hq) {
     const int node = (int)(((float)r + 0.5f) * p.inv_hq);
     const int hh = r - node * p.hq;
     const int h = (int)(((float)hh + 0.5f) * p.inv_G);
-    const int tile = (node * p.G + hh - h * p.G) / kRowsPerTile;
+    int rr = node * p.G + hh - h * p.G;                    // row of the stream's row group
     const int tiles = ceil_div(Nb * p.G, kRowsPerTile);
     int rgi = 0;
-    if (tiles > kBalWaves) rgi = tile / ceil_div(tiles, ceil_div(tiles, kBalWaves));
-    n_splits = p.ws_pieces[((size_t)b * p.hkv + h) * p.n_rg_max + rgi];
+    if (tiles > kBalWaves) {
+      const int rows = ceil_div(tiles, ceil_div(tiles, kBalWaves)) * kRowsPerTile;
+      rgi = rr / rows;
+      rr -= rgi * rows;
+    }
+    const int stream = (b * p.hkv + h) * p.n_rg_max + rgi;
+    const int pieces = p.ws_pieces[stream];
+    n_splits = pieces & 0xffff;
+    stride = p.slot_rows;
+    at0 = (size_t)start_slot(p, stream, pieces >> 16) * p.slot_rows + rr;
+    at1 = (size_t)(pieces >> 16) * p.slot_rows + rr;
   }
   const bool live = n_splits > 1 && r < Nb * p.hq;
-  const int row = node_base * p.hq + r;
-  const size_t stride = (size_t)p.total_nodes * p.hq;
   // A group folds BATCH of its splits at a time: their loads go out together,
   // those past the last split from the last one, and are not folded (a weight
   // of 0 would make an infinite output NaN). The reference starts below every
@@ -1295,10 +1306,11 @@ __global__ __launch_bounds__(kThreads) void split_merge_kernel(Params p, int chu
       float ms[BATCH], ls[BATCH], v[BATCH][8];
 #pragma unroll
       for (int k = 0; k < BATCH; ++k) {
-        const size_t pr = min(s0 + k * GROUPS, n_splits - 1) * stride + row;
+        const int s = min(s0 + k * GROUPS, n_splits - 1);
+        const size_t pr = s == 0 ? at0 : s * stride + at1;
         ms[k] = p.ws_m[pr];
         ls[k] = p.ws_l[pr];
-        load_partial8(static_cast<const T*>(p.ws_o) + pr * kD + d0, v[k]);
+        load_partial8(static_cast<const P*>(p.ws_o) + pr * kD + d0, v[k]);
       }
       float Mn = M;
 #pragma unroll
@@ -1401,16 +1413,17 @@ hipError_t launch_cascade_attention(const d2sd_attn_args& a, const AttnPlan& pla
     const int groups = plan.merge_groups;
     const long long chunks = merge_chunks_per_request(a.max_nodes, a.num_qo_heads, groups);
     const dim3 mgrid((unsigned)(a.batch * chunks));
-    if (a.dtype == D2SD_BF16) {
+    auto merge = [&](auto kernel) { hipLaunchKernelGGL(kernel, mgrid, dim3(kThreads), 0, stream, p, (int)chunks); };
+    const bool bf16 = a.dtype == D2SD_BF16;
+    if (plan.workgroups > 0) {
       if (groups > 1)
-        hipLaunchKernelGGL((split_merge_kernel<__bf16, 4>), mgrid, dim3(kThreads), 0, stream, p, (int)chunks);
+        merge(bf16 ? split_merge_kernel<__bf16, float, 4, true> : split_merge_kernel<float, float, 4, true>);
       else
-        hipLaunchKernelGGL((split_merge_kernel<__bf16, 1>), mgrid, dim3(kThreads), 0, stream, p, (int)chunks);
+        merge(bf16 ? split_merge_kernel<__bf16, float, 1, true> : split_merge_kernel<float, float, 1, true>);
+    } else if (groups > 1) {
+      merge(bf16 ? split_merge_kernel<__bf16, __bf16, 4, false> : split_merge_kernel<float, float, 4, false>);
     } else {
-      if (groups > 1)
-        hipLaunchKernelGGL((split_merge_kernel<float, 4>), mgrid, dim3(kThreads), 0, stream, p, (int)chunks);
-      else
-        hipLaunchKernelGGL((split_merge_kernel<float, 1>), mgrid, dim3(kThreads), 0, stream, p, (int)chunks);
+      merge(bf16 ? split_merge_kernel<__bf16, __bf16, 1, false> : split_merge_kernel<float, float, 1, false>);
     }
     e = hipGetLastError();
     if (ev[2]) (void)hipEventRecord(ev[2], stream);

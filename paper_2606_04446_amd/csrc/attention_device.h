@@ -26,13 +26,17 @@ struct Params {
   const uint32_t* anc_mask;
   void* out;
   float* lse;
-  void* ws_o;   // [n_ch_max, total_rows, D] split outputs normalised by their row sum, in the input dtype
-  float* ws_m;  // [n_ch_max, total_rows]
-  float* ws_l;  // [n_ch_max, total_rows]
-  int* ws_pieces;  // balanced shape: [batch, hkv, n_rg_max] pieces of a stream, else null
+  // Partial states: outputs normalised by their row sum, and m and l in fp32.
+  // Fixed splits: [n_ch_max, total_rows], outputs in the input dtype. Balanced:
+  // [slots, slot_rows], outputs in fp32.
+  void* ws_o;
+  float* ws_m;
+  float* ws_l;
+  int* ws_pieces;  // balanced: [batch, hkv, n_rg_max] (first workgroup << 16 | pieces) of a stream, else null
   int batch, hq, hkv, G, stage;
   int total_nodes, max_nodes, max_ctx, num_pages, max_pages, mask_words;
   int split, n_ch_max, n_rg_max, items;
+  int slot_rows;
   float c2;  // sm_scale * log2(e)
   float inv_G, inv_hq;   // reciprocals
 };
@@ -116,19 +120,29 @@ __device__ __forceinline__ float xhalf_max(float x) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Balanced: the slot of a stream's first piece, which workgroup `first` writes.
+// The other pieces' slots are their workgroups, which hold one each; the first
+// ones have slots by stream where there are no more streams than workgroups.
+__device__ __forceinline__ int start_slot(const Params& p, int stream, int first) {
+  return kBalWorkgroups + (p.batch * p.hkv * p.n_rg_max <= kBalWorkgroups ? stream : first);
+}
+
 inline Params make_params(const d2sd_attn_args& a, const AttnPlan& plan, void* ws) {
   Params p{};
   p.q = a.q; p.k_cache = a.k_cache; p.v_cache = a.v_cache; p.page_table = a.page_table;
   p.ctx_len = a.ctx_len; p.k_tree = a.k_tree; p.v_tree = a.v_tree; p.node_indptr = a.node_indptr;
   p.anc_mask = a.anc_mask; p.out = a.out; p.lse = a.lse;
-  const size_t rows = (size_t)a.total_nodes * a.num_qo_heads;
-  // [normalised O in the input dtype][m][l] (fp32), each split-major
+  // [O][m][l], each split- or slot-major, then the piece counts
   char* w = static_cast<char*>(ws);
-  const size_t o_bytes = (size_t)plan.n_ch_max * rows * kD * (a.dtype == D2SD_BF16 ? 2 : 4);
+  const bool balanced = plan.workgroups > 0;
+  const size_t states = balanced ? (size_t)plan.slots * plan.slot_rows
+                                 : (size_t)plan.n_ch_max * a.total_nodes * a.num_qo_heads;
+  const size_t o_bytes = states * kD * (a.dtype == D2SD_BF16 && !balanced ? 2 : 4);
   p.ws_o = w;
   p.ws_m = w ? reinterpret_cast<float*>(w + o_bytes) : nullptr;
-  p.ws_l = w ? p.ws_m + (size_t)plan.n_ch_max * rows : nullptr;
-  p.ws_pieces = w && plan.workgroups > 0 ? reinterpret_cast<int*>(p.ws_l + (size_t)plan.n_ch_max * rows) : nullptr;
+  p.ws_l = w ? p.ws_m + states : nullptr;
+  p.ws_pieces = w && balanced ? reinterpret_cast<int*>(p.ws_l + states) : nullptr;
+  p.slot_rows = plan.slot_rows;
   p.batch = a.batch; p.hq = a.num_qo_heads; p.hkv = a.num_kv_heads; p.G = plan.G; p.stage = a.stage;
   p.total_nodes = a.total_nodes; p.max_nodes = a.max_nodes; p.max_ctx = a.max_ctx_len;
   p.num_pages = a.num_pages; p.max_pages = a.max_pages; p.mask_words = a.mask_words;

@@ -10,9 +10,13 @@
 // lengths are known to the device only: each workgroup reads them (and the
 // node offsets), scans the costs and finds its own share. A share holds the
 // end of one stream, whole streams, the start of another; each part is a
-// piece. A stream that is one piece is finalised in place; otherwise piece k
-// writes the partial state of split k, and the number of pieces goes to the
-// workspace for the split merge.
+// piece. A stream that is one piece is finalised in place; otherwise every
+// piece writes a partial state, and the number of pieces and the workgroup of
+// the first go to the workspace for the split merge. A workgroup has at most
+// one piece that continues a stream and one that a later workgroup continues,
+// so two slots per workgroup hold all partial states. Their outputs are fp32: rounded to
+// bf16 a piece costs as much accuracy as the rounding of the result, however
+// many there are.
 //
 // Twelve waves, one query tile each. The key tiles go through a ring of LDS
 // slots filled by LDS DMA, several steps deep: a piece is a short stream whose
@@ -395,19 +399,19 @@ __device__ __forceinline__ void bal_read_q(const char* area, int lane, int pass,
   }
 }
 
-// The wave's output rows, scaled by inv, to rows of `dst` by way of LDS, so
-// that a store instruction writes whole rows (four of bf16, two of fp32). fp32
-// goes in two passes of 16 rows.
+// The wave's output rows, scaled by inv, as type Out to row_at(row) by way of
+// LDS, so that a store instruction writes whole rows (four of bf16, two of
+// fp32). fp32 goes in two passes of 16 rows.
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
-template <typename T>
-__device__ __forceinline__ void bal_store(const Params& p, const BalRows& rw, char* dst, char* area, int lane,
-                                          f32x16 (&o)[4], float inv) {
-  constexpr int PASSES = sizeof(T) / 2;
-  constexpr int STRIDE = BalTile<T>::ROW_BYTES + 16;        // of a staged row
-  constexpr int LANES = BalTile<T>::ROW_BYTES / 16;         // per row
+template <typename T, typename Out, typename Row>
+__device__ __forceinline__ void bal_store(const BalRows& rw, char* area, int lane, f32x16 (&o)[4], float inv, Row row_at) {
+  constexpr int ROW_BYTES = kD * sizeof(Out);
+  constexpr int PASSES = sizeof(Out) / 2;
+  constexpr int STRIDE = ROW_BYTES + 16;                    // of a staged row
+  constexpr int LANES = ROW_BYTES / 16;                     // per row
   constexpr int ROWS = kRowsPerTile / PASSES;               // per pass
   const int hf = lane >> 5, r = lane & 31;
 #pragma unroll
@@ -422,6 +426,15 @@ __device__ __forceinline__ void bal_store(const Params& p, const BalRows& rw, ch
         for (int q4 = 0; q4 < 4; ++q4)
           *reinterpret_cast<uint2*>(mine + dt * 64 + q4 * 16 + hf * 8) =
               make_uint2(pack_bf16(o[dt][4 * q4], o[dt][4 * q4 + 1]), pack_bf16(o[dt][4 * q4 + 2], o[dt][4 * q4 + 3]));
+    } else if constexpr (sizeof(T) == 2) {
+      if (r / ROWS == pass) {
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+          for (int q4 = 0; q4 < 4; ++q4)
+            *reinterpret_cast<float4*>(mine + dt * 128 + q4 * 32 + hf * 16) =
+                make_float4(o[dt][4 * q4], o[dt][4 * q4 + 1], o[dt][4 * q4 + 2], o[dt][4 * q4 + 3]);
+      }
     } else {
       if (r / ROWS == pass) {      // a register at a time: four adjacent dims sit in four accumulators
 #pragma unroll
@@ -436,8 +449,7 @@ __device__ __forceinline__ void bal_store(const Params& p, const BalRows& rw, ch
       const int rr = i * (kWave / LANES) + lane / LANES;
       const uint4 v = lds_b128(area, rr * STRIDE + (lane % LANES) * 16);
       const int row = rw.row0 + pass * ROWS + rr;
-      if (row < rw.rows)
-        *reinterpret_cast<uint4*>(dst + rw.global_row(p, row) * BalTile<T>::ROW_BYTES + (lane % LANES) * 16) = v;
+      if (row < rw.rows) *reinterpret_cast<uint4*>(row_at(row) + (lane % LANES) * 16) = v;
     }
   }
 }
@@ -583,8 +595,7 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
     end[k] = in ? p.node_indptr[b + 1] : 0;
     ctx[k] = in ? p.ctx_len[b] : 0;
   }
-  int sum = 0, count = 0, top_cost = 1, top_work = 0;
-  int cost[bal::PER_LANE];
+  int sum = 0, count = 0, top_cost = 1;
   for (int k = 0; k < per; ++k) {
     const int b = lane * per + k;
     int nd = 0, en = 0, cx = 0;
@@ -603,18 +614,14 @@ __device__ __forceinline__ void bal_schedule(const Params& p, BalShared<T>& sh, 
     sum += r.streams * r.work;
     count += r.streams;
     top_cost = max(top_cost, r.streams ? r.cost : 1);
-    top_work = max(top_work, r.streams ? r.n_tiles * r.cost : 0);
   }
   // The start of a stream counts as four shares of the tiles at most: where
   // shares are short, more would leave workgroups without any tile.
   const int incl = wave_scan<false>(sum), incl_count = wave_scan<false>(count);
   const int start = min(BalTile<T>::OVERHEAD, 4 * ceil_div(lane_of(incl, 63), kBalWorkgroups));
   const int total = lane_of(incl, 63) + start * lane_of(incl_count, 63);
-  // A share is at least one tile (every piece then holds a tile) and long
-  // enough that no stream falls into more than n_ch_max pieces.
-  int share = max(ceil_div(total, kBalWorkgroups), lane_of(wave_scan<true>(top_cost), 63));
-  top_work = lane_of(wave_scan<true>(top_work), 63);
-  if (share * (p.n_ch_max - 1) < top_work) share = ceil_div(top_work, p.n_ch_max - 1);
+  // A share is at least one tile: every piece then holds a tile.
+  const int share = max(ceil_div(total, kBalWorkgroups), lane_of(wave_scan<true>(top_cost), 63));
   const int lo = (int)blockIdx.x * share;
   if (lane == 0) {
     sh.share = share;
@@ -884,7 +891,8 @@ void cascade_balanced_kernel(Params p) {
     if (wave_s == bal::WAVES - 1) {
       if (!pc.last) bal_seek<T>(p, sh, batch, pc.b, pc.sidx + 1, sh.piece[turn ^ 1], lane);
       else if (lane == 0) sh.piece[turn ^ 1].count = 0;
-      if (lane == 0 && pc.index == 0) p.ws_pieces[((size_t)pc.b * p.hkv + pc.h) * p.n_rg_max + pc.rgi] = pc.count;
+      if (lane == 0 && pc.index == 0)
+        p.ws_pieces[((size_t)pc.b * p.hkv + pc.h) * p.n_rg_max + pc.rgi] = (int)blockIdx.x << 16 | pc.count;
     }
 
     if constexpr (BT::MAX_KG == 2) {
@@ -927,20 +935,29 @@ void cascade_balanced_kernel(Params p) {
     if (active && kg == 0) {
       const float l_all = st.l + __shfl_xor(st.l, 32);
       const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
+      char* const rows_area = sh.ring + wave_s * BalTile<__bf16>::K_BYTES;
       const bool direct = pc.count == 1;
-      const size_t part = direct ? 0 : (size_t)pc.index * ((size_t)p.total_nodes * p.hq);
-      bal_store<T>(p, rw, static_cast<char*>(direct ? p.out : p.ws_o) + part * BT::ROW_BYTES,
-                   sh.ring + wave_s * BalTile<__bf16>::K_BYTES, fresh(lane), st.o, inv);
+      const int stream = (pc.b * p.hkv + pc.h) * p.n_rg_max + pc.rgi;
+      const int slot = pc.index > 0 ? (int)blockIdx.x : start_slot(p, stream, blockIdx.x);
+      const size_t part = (size_t)slot * p.slot_rows;       // the piece's first row in the workspace
       const int ln = fresh(lane);
       const int r = rw.row0 + ln;
       if (ln < kRowsPerTile && r < rw.rows) {
-        const size_t row = part + rw.global_row(p, r);
         if (!direct) {
-          p.ws_m[row] = l_all > 0.0f ? st.m : -INFINITY;
-          p.ws_l[row] = l_all;
+          p.ws_m[part + r - pc.row0] = l_all > 0.0f ? st.m : -INFINITY;
+          p.ws_l[part + r - pc.row0] = l_all;
         } else if (p.lse) {
-          p.lse[row] = l_all > 0.0f ? (st.m + __log2f(l_all)) * kLn2 : -INFINITY;
+          p.lse[rw.global_row(p, r)] = l_all > 0.0f ? (st.m + __log2f(l_all)) * kLn2 : -INFINITY;
         }
+      }
+      auto to_out = [&](int row) { return static_cast<char*>(p.out) + rw.global_row(p, row) * BT::ROW_BYTES; };
+      auto to_slot = [&](int row) { return static_cast<char*>(p.ws_o) + (part + row - pc.row0) * (kD * sizeof(float)); };
+      if constexpr (sizeof(T) == 4) {
+        bal_store<T, T>(rw, rows_area, fresh(lane), st.o, inv, [&](int row) { return direct ? to_out(row) : to_slot(row); });
+      } else if (direct) {
+        bal_store<T, T>(rw, rows_area, fresh(lane), st.o, inv, to_out);
+      } else {
+        bal_store<T, float>(rw, rows_area, fresh(lane), st.o, inv, to_slot);
       }
     }
   }

@@ -57,6 +57,8 @@ struct AttnPlan {
   long long tiles;   // packed: query tiles of all streams (the grid holds ceil(tiles / 12) workgroups)
   int split;         // context tokens per split (multiple of 64)
   int n_ch_max;      // splits of the longest context (>= 1); balanced: most pieces of a stream
+  int slots;         // balanced: partial states the workspace holds, of slot_rows rows each
+  int slot_rows;     // rows of the largest row group
   int n_rg_max;      // row groups of the largest request (>= 1)
   long long items;   // batch * hkv * n_ch_max * n_rg_max
   size_t ws_bytes;   // partial-state workspace (0 when n_ch_max == 1)

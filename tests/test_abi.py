@@ -448,6 +448,22 @@ def test_where_the_keys_are_divided_evenly(dtype, batch, hq, hkv, ctx, nodes, ev
     assert d2sd.cascade_division(a)[0] == even
 
 
+@pytest.mark.parametrize("dtype,batch,hq,hkv,ctx,nodes", [
+    (0, 1, 32, 8, 32768, 48), (0, 8, 32, 8, 8192, 48), (0, 24, 64, 8, 4096, 48), (1, 4, 32, 8, 3000, 48),
+    (1, 128, 32, 8, 1000, 48), (1, 256, 32, 8, 2048, 64), (1, 2, 8, 1, 1000, 200), (0, 2, 16, 2, 50000, 300)])
+def test_even_division_workspace_holds_two_pieces_per_cu(dtype, batch, hq, hkv, ctx, nodes):
+    """A workgroup continues one stream at most and leaves one to the next at
+    most: 256 slots and one per stream (up to 512), of a row group's rows in
+    fp32 with m and l, and a word per stream, whatever the contexts are."""
+    a = good_args(dtype=(d2sd.BF16, d2sd.F32)[dtype], batch=batch, num_qo_heads=hq, num_kv_heads=hkv, max_ctx_len=ctx,
+                  total_nodes=batch * nodes, max_nodes=nodes, max_pages=4096, num_pages=batch * 4096,
+                  mask_words=(nodes + 31) // 32)
+    tiles = -(-nodes * (hq // hkv) // 32)
+    streams = batch * hkv * -(-tiles // 12)
+    assert d2sd.cascade_division(a)[0]
+    assert ws_size(a) == (d2sd.OK, (256 + min(256, streams)) * 32 * min(tiles, 12) * 520 + 4 * streams)
+
+
 def test_noncascade_validation():
     a = good_args(stage=d2sd.STAGE_PREFIX)
     assert d2sd._noncascade(ctypes.byref(a), None) == d2sd.ERR_INVALID_ARG

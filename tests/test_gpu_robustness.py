@@ -16,6 +16,7 @@ import torch
 
 from paper_2606_04446_amd import workload as wl
 from tests.gpu_cases import Case
+from tests.test_gpu_balanced import even_layout
 
 pytestmark = pytest.mark.gpu
 
@@ -131,6 +132,42 @@ def test_twelve_wave_attention_with_inconsistent_device_arrays(shape):
     for k, v in inputs.items():
         assert torch.equal(x[k], v), k
     again, again_lse = c.attention(kv_split=1024, host_offsets=True, row_group=384, packed=opt["packed"])
+    torch.cuda.synchronize()
+    assert torch.equal(again, ref) and torch.equal(again_lse, ref_lse)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_even_division_with_inconsistent_device_arrays(dtype):
+    """The even division finds its streams, pieces and workspace slots from the
+    device arrays; the merge finds them again from the same ones."""
+    m = d2sd()
+    c = Case(even_layout(16, [[3, 7], [2], [], [5, 9, 12], [1]], [3000, 40, 0, 2570, 700], hq=8, hkv=2, dtype=dtype, seed=4))
+    x = c.x
+    assert m.cascade_division(c._args())[0]
+    max_ctx = int(c.layout.ctx_len.max())
+    ref, ref_lse = c.attention()
+    torch.cuda.synchronize()
+    inputs = {k: v.clone() for k, v in x.items()}
+    for seed in range(4):
+        rng = np.random.default_rng([9, seed, int(dtype == "bf16")])
+        bad_ip, bad_ctx = garbage_i32(rng, c.layout.batch + 1), garbage_i32(rng, c.layout.batch)
+        bad_pt = garbage_i32(rng, c.d_pt.numel()).view_as(c.d_pt)
+        if seed == 0:                                  # every request claims all rows and the longest context
+            bad_ip = torch.tensor([0, c.total] * (c.layout.batch + 1), dtype=torch.int32, device="cuda")[:c.layout.batch + 1]
+            bad_ctx = torch.full_like(bad_ctx, INT_MAX)
+        obuf, out = guarded(tuple(x["q"].shape), x["q"].dtype, 7.0)
+        lbuf, lse = guarded(tuple(x["q"].shape[:2]), torch.float32, 7.0)
+        need = m.cascade_workspace_size(c._args())
+        wbuf, ws = guarded((need,), torch.uint8, 0x5A)
+        m.cascade_verify_attention(x["q"], x["k_cache"], x["v_cache"], bad_pt, bad_ctx, x["k_tree"], x["v_tree"],
+                                   bad_ip, c.tree["anc_mask"], total_nodes=c.total, max_nodes=c.max_nodes,
+                                   max_ctx_len=max_ctx, out=out, lse=lse, workspace=ws)
+        torch.cuda.synchronize()
+        assert guard_intact(obuf, out.shape, 7.0) and guard_intact(lbuf, lse.shape, 7.0)
+        assert guard_intact(wbuf, ws.shape, 0x5A)
+    for k, v in inputs.items():
+        assert torch.equal(x[k], v), k
+    again, again_lse = c.attention()
     torch.cuda.synchronize()
     assert torch.equal(again, ref) and torch.equal(again_lse, ref_lse)
 

@@ -72,6 +72,38 @@ def test_automatic_plan_larger_than_the_scratch():
         assert max(max_abs(o_h[s:e], ow), max_abs(l_h[s:e], lw)) <= tol, b
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_even_division_that_fits(dtype):
+    """An even division whose partial states fit runs from the scratch as it
+    does from a workspace."""
+    case = Case(wl.custom_layout(16, [[3, 9], [1, 2, 14], []] * 3, [9000, 700, 1] * 3, hq=32, hkv=8, dtype=dtype, seed=6))
+    assert d2sd().cascade_division(case._args())[0]
+    (o, l), (o_ref, l_ref), ws = call_both(case)
+    assert 0 < ws <= SCRATCH_BYTES
+    assert torch.equal(o, o_ref) and torch.equal(l, l_ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_even_division_larger_than_the_scratch(dtype):
+    """24 ragged requests of up to twelve query tiles and 192 streams: the slots
+    of the even division hold 89 MB, so the call takes fixed splits that fit."""
+    rng = np.random.default_rng(15)
+    p = [[4, 8, 12, 14]] + [sorted(rng.choice(np.arange(1, 16), int(rng.integers(0, 4)), replace=False).tolist()) for _ in range(23)]
+    p = [r if sum(16 - x for x in r) <= 26 else r[-1:] for r in p]
+    ctx = [2000] + rng.integers(1, 1900, 23).tolist()
+    case = Case(wl.custom_layout(16, p, ctx, hq=64, hkv=8, dtype=dtype, seed=16))
+    assert d2sd().cascade_division(case._args())[0]
+    (o, l), (o_ref, l_ref), ws = call_both(case)
+    assert ws > SCRATCH_BYTES
+    tol = TOL[dtype]
+    assert max_abs(o.double().cpu().numpy(), o_ref.double().cpu().numpy()) <= tol
+    assert max_abs(l.cpu().numpy(), l_ref.cpu().numpy()) <= tol
+    for b in (0, 5, 23):
+        s, e = int(case.node_indptr[b]), int(case.node_indptr[b + 1])
+        ow, lw = case.oracle_attention(b)
+        assert max(max_abs(o[s:e].double().cpu().numpy(), ow), max_abs(l[s:e].cpu().numpy(), lw)) <= tol, b
+
+
 def test_explicit_split_larger_than_the_scratch_is_rejected():
     m = d2sd()
     case = Case(wl.draw_layout(3))
