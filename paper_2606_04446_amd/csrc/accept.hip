@@ -17,7 +17,10 @@
 // are kept, so that the chosen path's nodes are found by all depths at once.
 // On 1 / 8 / 16 requests of 48-80 nodes, from launch to end: 3.7 / 5.5 / 5.4 us
 // when one lane walked the path, 3.2 / 4.9 / 5.0 us now; what is left is the
-// launch and the two dependent loads.
+// launch and the two dependent loads. The tables hold the match flags too:
+// 52 KB keep three workgroups on a CU. With flags of their own and a level that
+// nothing reads, 60 KB and two, 4096 requests took 17.6 us, now 11.7 (15.1 when
+// one lane walked the path).
 #include "launchers.h"
 
 namespace d2sd {
@@ -26,15 +29,19 @@ namespace {
 
 constexpr int kAcceptThreads = 256;
 constexpr int kMaxNodes = D2SD_MAX_B + D2SD_MAX_B * (D2SD_MAX_B - 1) / 2;  // 2080
-constexpr int kLevels = 7;             // 2^0 .. 2^6 covers every distance below D2SD_MAX_B
+constexpr int kLevels = 6;             // 2^0 .. 2^5 add up to every distance below D2SD_MAX_B
+// An entry of the ancestor tables: the ancestor's index + 1 (0: none), and
+// whether all links up to it match.
+constexpr int kOk = 1 << 12;
+static_assert(kMaxNodes < kOk, "index bits");
+static_assert(3 * (kMaxNodes * (2 * kLevels + 1 + 3 * 4) + 256) <= 160 * 1024, "three workgroups on a CU");
 
 __global__ __launch_bounds__(kAcceptThreads) void accept_path_kernel(
     int B, const int* __restrict__ node_indptr, int total_nodes, const int* __restrict__ parent,
     const int* __restrict__ depth, const int* __restrict__ path_id, const int* __restrict__ draft,
     const int* __restrict__ argmax, int* __restrict__ accept_len, int* __restrict__ best_path,
     int* __restrict__ accept_node, int* __restrict__ path_nodes, int* __restrict__ out_tokens) {
-  __shared__ uint8_t s_ok[2][kMaxNodes];
-  __shared__ short s_up[kLevels][kMaxNodes];   // 2^r-th ancestor, or -1
+  __shared__ uint16_t s_up[kLevels][kMaxNodes];   // of the 2^r-th ancestor
   __shared__ uint8_t s_dep[kMaxNodes];
   __shared__ int s_tok[kMaxNodes];
   __shared__ int s_arg[kMaxNodes];
@@ -49,7 +56,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_path_kernel(
   for (int c = t; c < Nb; c += kAcceptThreads) {
     int par = parent[base + c];
     if (par < 0 || par >= c) par = -1;   // canonical order puts parents first
-    s_up[0][c] = (short)par;
+    s_up[0][c] = (uint16_t)(par + 1);
     s_tok[c] = draft[base + c];
     s_arg[c] = argmax[base + c];
     s_pid[c] = path_id[base + c];
@@ -57,31 +64,27 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_path_kernel(
   }
   __syncthreads();
   for (int c = t; c < Nb; c += kAcceptThreads) {
-    const short par = s_up[0][c];
-    s_ok[0][c] = par < 0 || s_tok[c] == s_arg[par];
+    const int up = s_up[0][c];
+    if (up == 0 || s_tok[c] == s_arg[up - 1]) s_up[0][c] = (uint16_t)(up | kOk);
   }
   __syncthreads();
-  int cur = 0, level = 0;
-  for (int span = 1; span < B; span *= 2, ++level) {
-    for (int c = t; c < Nb; c += kAcceptThreads) {
-      uint8_t ok = s_ok[cur][c];
-      short up = s_up[level][c];
-      if (up >= 0) {
-        ok &= s_ok[cur][up];
-        up = s_up[level][up];
-      }
-      s_ok[cur ^ 1][c] = ok;
-      s_up[level + 1][c] = up;
-    }
+  // An entry joined with its ancestor's reaches twice as far.
+  auto joined = [&](int level, int c) {
+    const int e = s_up[level][c];
+    const int up = e & (kOk - 1);
+    return up == 0 ? e : s_up[level][up - 1] & (e | (kOk - 1));
+  };
+  int level = 0;
+  for (; 2 << level < B; ++level) {
+    for (int c = t; c < Nb; c += kAcceptThreads) s_up[level + 1][c] = (uint16_t)joined(level, c);
     __syncthreads();
-    cur ^= 1;
   }
 
   // key = depth * 65536 + (65535 - index) over accepted nodes; the root is
   // always accepted, so the maximum exists whenever Nb > 0.
   int best = -1;
   for (int c = t; c < Nb; c += kAcceptThreads)
-    if (s_ok[cur][c]) best = max(best, (int)s_dep[c] * 65536 + (65535 - c));
+    if (joined(level, c) & kOk) best = max(best, (int)s_dep[c] * 65536 + (65535 - c));
   // every key but "none" is >= 0; the scan's last lane holds the maximum
   const int top = lane_of(wave_scan<true>(best + 1), kWave - 1) - 1;
   if ((t % kWave) == 0) s_best[t / kWave] = top;
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(kAcceptThreads) void accept_path_kernel(
   // digits; all depths at once instead of a walk of L dependent reads.
   int node = t <= L ? chosen : -1;
   for (int r = 0, steps = L - t; r < kLevels && (1 << r) <= L; ++r)
-    if (node >= 0 && ((steps >> r) & 1)) node = s_up[r][node];
+    if (node >= 0 && ((steps >> r) & 1)) node = (s_up[r][node] & (kOk - 1)) - 1;
   const int next = __shfl_down(node, 1);       // the path's node at depth d + 1
   if (t < B) {
     int tok = -1;
