@@ -28,9 +28,11 @@ __device__ __forceinline__ double lane_of(double x, int src) {
 }
 
 // Latency-bound: one wave per request and a chain of n products. Each lane
-// holds one confidence and one posterior, and the others reach it by lane
-// reads. With a load and an LDS read per step of the two loops 64 requests of
-// 15 confidences took 4.0 us, now 3.3.
+// holds one confidence and one posterior; the chain reaches the confidences by
+// lane reads, the ranking the posteriors in LDS (whose reads run ahead of the
+// comparisons). With a load per step of the chain 64 requests of 15
+// confidences took 3.5 us, now 3.0; of 63, 7.7 and 6.1; 4096 of 63, 10.5 and
+// 9.5 (11.0 with the posteriors by lane reads, four vector instructions each).
 #pragma clang fp contract(off)
 __global__ __launch_bounds__(kSelectThreads) void select_reanchor_kernel(
     int B, int Kmax, const float* __restrict__ conf, const int* __restrict__ K, int* __restrict__ p_out,
@@ -50,9 +52,12 @@ __global__ __launch_bounds__(kSelectThreads) void select_reanchor_kernel(
   // ranks below every number, so the order stays total and exactly Kb
   // prefix lengths are kept.
   const double key = __builtin_isnan(r) ? -INFINITY : r;
+  __shared__ double s_key[kSelectThreads];
+  s_key[i] = key;
+  __syncthreads();
   int rank = 0;                         // prefix lengths ordered before i
   for (int j = 0; j < n; ++j) {
-    const double rj = lane_of(key, j);
+    const double rj = s_key[j];
     rank += (rj > key) || (rj == key && j < i);
   }
   const bool keep = i < n && rank < Kb;
