@@ -278,28 +278,34 @@ __global__ __launch_bounds__(kSampleThreads) void sample_targets_kernel(
   if (c >= Nb) return;
 
   // ---- representative: the lowest-index node with the same root path tokens.
-  // Only a node with this node's own token can be one, and few trees hold it
-  // twice: the paths are looked at only where one does.
+  // Only a node with this node's own token can be one: the paths are looked at
+  // only where an earlier node has it.
   const int tok_c = draft[base + c];
   bool twin = false;
-  for (int x = t; x < c; x += kSampleThreads) twin |= draft[base + x] == tok_c;
+  for (int x = t; x <= c; x += kSampleThreads) {
+    int par = parent[base + x];
+    if (par < 0 || par >= x) par = -1;          // parents precede children
+    const int tok = draft[base + x];
+    s_par[x] = (short)par;
+    s_tok[x] = tok;
+    twin |= x < c && tok == tok_c;
+  }
   // The node is usually its own representative: the first loads of its row go
-  // out now (after the tokens above, whose wait would otherwise include them)
+  // out now (after the staging above, whose wait would otherwise include them)
   // and are in flight during the search below.
   const int n_steps = ceil_div(V, SE);
   const int n_whole = V / SE;                   // steps lying wholly inside the row
   const void* row_c = static_cast<const char*>(logits) + (size_t)(base + c) * (size_t)V * kEltBytes;
   uint4 raw[kResident][kLoadsPerStep];
   load_full<DT>(raw, row_c, w, n_whole, lane);
+  const uint64_t wave_twins = __ballot(twin);
+  if (lane == 0) s_best[w] = wave_twins != 0;
+  __syncthreads();
+  bool twins = false;
+#pragma unroll
+  for (int i = 0; i < kSampleWaves; ++i) twins |= s_best[i] != 0;
   int rep = c;
-  if (__syncthreads_or(twin)) {
-    for (int x = t; x <= c; x += kSampleThreads) {
-      int par = parent[base + x];
-      if (par < 0 || par >= x) par = -1;          // parents precede children
-      s_par[x] = (short)par;
-      s_tok[x] = draft[base + x];
-    }
-    __syncthreads();
+  if (twins) {
     if (t == 0) {
       int x = c, d = 0;
       while (s_par[x] >= 0 && d < D2SD_MAX_B) {
