@@ -22,10 +22,6 @@ constexpr int kIndptrThreads = 256;
 __device__ __forceinline__ float lane_of(float x, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), src));
 }
-__device__ __forceinline__ double lane_of(double x, int src) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
-                          __builtin_amdgcn_readlane(__double2loint(x), src));
-}
 
 // Latency-bound: one wave per request and a chain of n products. Each lane
 // holds one confidence and one posterior; the chain reaches the confidences by
