@@ -273,9 +273,15 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
   return d2sd::kBalWorkgroups;
 }
 
+struct Shape {
+  int waves;
+  bool packed;
+  int splits;
+};
+
 // Where the even division beats the fixed splits (attention with its merge on
-// the GPU, us, fixed splits first; 32/8 heads unless said; `splits` and g4: the
-// fixed plan's split count and its row groups per split). Never without context
+// the GPU, us, fixed splits first; 32/8 heads unless said). fixed is the plan
+// that it would replace, g4 its row groups per split. Never without context
 // keys (the tree stage is one launch and needs no workspace) and never for an
 // empty batch.
 //  - bf16, grids that do not fill the chip with one split: its start, stores and
@@ -284,42 +290,47 @@ int balanced_workgroups(const d2sd_attn_args* a, int G) {
 //    1000: 27 -> 35, of 4k: 61 -> 56, of 0.5-4k: 56 -> 42; 8/2 heads, 4 of 4k:
 //    20 -> 27, of 16k: 41 -> 38), and with few query tiles a stream, whose key
 //    tiles cost less, more of them: 80 pairs of a key and a query tile a CU
-//    (16/8 heads, 2-3 tiles: 2 of 8k 27 -> 30, 8 of 8k 77 -> 61). Contexts below
-//    1250 tokens have too few tiles a stream (32 of 1000: 64 -> 69).
-//    Of 1237 batches of 1-47 requests, 400-32k tokens and four head counts the
-//    rule takes 473, 10% faster in the mean, 6 of them slower by 4-12%.
-//  - bf16, larger grids: not at all. One split fills the chip there, and every
-//    row goes from registers to the output. With five to eight query tiles per
-//    stream: 64 requests of 1k 94 -> 118; 64 of 2k-8k 365 -> 375; 48 of 16k
-//    909 -> 936; 96 of 16k 1824 -> 1848; 192 of 4k 977 -> 994 (64 of 16k
-//    1189 -> 1162); with fewer 64 of 8000: 391 -> 398; with more 32 of 16k:
-//    837 -> 857, 64 of 32k, 64/8 heads: 5.3 -> 6.3 ms.
+//    (16/8 heads, 2-3 tiles: 2 of 8k 27 -> 30, 8 of 8k 77 -> 61); with 150 pairs
+//    14 key tiles are enough (9 of 0.2-2k: 74 -> 54). Contexts below 1250 tokens
+//    have too few tiles a stream (32 of 1000: 64 -> 69).
+//    Of 1785 batches of 1-64 requests, 400-32k tokens and five head counts the
+//    rule takes half, 10% faster in the mean, 19 of them slower by 4-12%.
+//  - bf16, larger grids, which one split fills: where the fixed plan is the
+//    four-wave shape with five to eight query tiles a stream, so that it reads
+//    every context twice, from 1600 tokens on (64 of 16k, 31-63 nodes: 1189 ->
+//    1129; of 111 batches of 30-240 requests, 11% faster in the mean, 4 slower by
+//    4-6%; below 1600 tokens up to 22% slower). Not where it is a twelve-wave
+//    shape: packed, 48 of 16k and 60 nodes 909 -> 936, 192 of 4k 977 -> 994, 64 of
+//    2k-8k 365 -> 375, at worst 20%; one stream, 32 of 16k 837 -> 857; packed with
+//    64/8 heads, 64 of 32k 5.3 -> 6.3 ms. With fewer tiles level (64 of 8000: 391 ->
+//    398).
 //  - fp32: from more than one split's minimum on (1 request of 100 tokens: 46 ->
 //    28; 16 of 4000: 974 -> 463; 64 of 500: 569 -> 311), but not where the fixed
 //    plan is one unsplit round that fills the CUs with a short context (16 of 66:
 //    43 -> 54, of 100: 49 -> 59, of 200: 69 -> 71; 64/8 heads, 4 of 66: 35 -> 39).
-bool balanced_pays(const d2sd_attn_args* a, bool large_grid, long long g4, int splits) {
+bool balanced_pays(const d2sd_attn_args* a, int G, const Shape& fixed, bool large_grid, long long g4) {
   if (a->stage == D2SD_STAGE_TREE || a->total_nodes == 0) return false;
   const long long ctx = a->max_ctx_len;
   if (a->dtype == D2SD_F32) {
-    const bool one_round = splits == 1 && g4 <= kNumCUs && g4 >= (ctx < 96 ? 40 : 150);
+    const bool full_groups = (long long)a->total_nodes * G >= 128ll * a->batch;
+    const bool one_round = fixed.splits == 1 && g4 <= kNumCUs && g4 >= (ctx < 96 && full_groups ? 75 : 150);
     return ctx > kMinSplitF32 && !(one_round && ctx < 200);
   }
   constexpr long long kTile = 32;   // keys, and rows of a query tile
-  return !large_grid && ctx >= 1250 && ctx * a->batch * a->num_kv_heads >= 20 * kTile * kNumCUs &&
-         ctx * a->total_nodes * a->num_qo_heads >= 80 * kTile * kTile * kNumCUs;
+  if (large_grid) {
+    const long long tiles = ((long long)a->max_nodes * G + kTile - 1) / kTile;
+    return fixed.waves == d2sd::kBf16Waves && tiles > 4 && tiles <= 8 && ctx >= 1600;
+  }
+  // per CU: key tiles, and pairs of a key and a query tile
+  const long long keys = ctx * a->batch * a->num_kv_heads / (kTile * kNumCUs);
+  const long long pairs = ctx * a->total_nodes * a->num_qo_heads / (kTile * kTile * kNumCUs);
+  return ctx >= 1250 && ((keys >= 20 && pairs >= 80) || (keys >= 14 && pairs >= 150));
 }
 
 // Most pieces a stream of the balanced shape is cut into: a request's streams,
 // one per KV head at least, are equal parts of the line of costs, so each has
 // at most this share of the workgroups (and pieces at both ends).
 int balanced_pieces(const d2sd_attn_args* a) { return kNumCUs / a->num_kv_heads + 2; }
-
-struct Shape {
-  int waves;
-  bool packed;
-  int splits;
-};
 
 // Packing streams costs extra reads of the streams it cuts and some control
 // work per round; it has to beat the one-stream 12-wave shape by 3%.
@@ -400,7 +411,7 @@ void choose_shape(const d2sd_attn_args* a, int G, d2sd::AttnPlan* plan, bool eve
     const int s = (int)((2 * R4 + g4 - 1) / g4);
     sh.splits = max(s_lo, min(s, s_hi));
   }
-  if (even && a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, g4 * s_lo >= R4, g4, sh.splits))
+  if (even && a->kv_split == 0 && a->row_group == 0 && !(pk_ok && a->packed == 2) && balanced_pays(a, G, sh, g4 * s_lo >= R4, g4))
     plan->workgroups = balanced_workgroups(a, G);
   if (plan->workgroups > 0) sh = Shape{d2sd::kBf16Waves, false, sh.splits};
   plan->waves = sh.waves;

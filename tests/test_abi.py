@@ -425,16 +425,29 @@ def test_calls_without_context_keys_or_rows_need_no_workspace(dtype):
 
 @pytest.mark.parametrize("batch,ctx,nodes", [(64, 1024, 44), (48, 16384, 60), (96, 16384, 60), (192, 4096, 64)])
 def test_bf16_grids_that_fill_the_chip_keep_whole_streams(batch, ctx, nodes):
-    """Streams of five to eight query tiles that fill the chip with one split:
-    no stream is cut, and no workspace is needed."""
+    """Streams of five to eight query tiles that fill the chip with one split of
+    the packed shape, or of fewer than 1600 tokens: no stream is cut, and no
+    workspace is needed."""
     ip = np.arange(batch + 1, dtype=np.int32) * nodes
     a = _with_host_indptr(good_args(batch=batch, total_nodes=batch * nodes, max_nodes=nodes, max_ctx_len=ctx,
                                     max_pages=1024, num_pages=batch * 1024), ip)
     assert d2sd.cascade_division(a) == (False, 1) and ws_size(a) == (d2sd.OK, 0)
 
 
+@pytest.mark.parametrize("ctx,most,even", [(1599, 48, False), (1600, 48, True), (16384, 48, True), (16384, 64, True),
+                                           (16384, 66, False), (16384, 30, False)])
+def test_large_bf16_grids_of_the_four_wave_shape(ctx, most, even):
+    """160 requests, one in two of the smallest tree (so that the packed shape
+    does not apply): divided evenly with five to eight query tiles."""
+    ip = np.concatenate([[0], np.cumsum([16, most] * 80)]).astype(np.int32)
+    a = _with_host_indptr(good_args(batch=160, total_nodes=int(ip[-1]), max_nodes=most, max_ctx_len=ctx,
+                                    max_pages=1024, num_pages=160 * 1024), ip)
+    assert d2sd.cascade_division(a)[0] == even
+
+
 @pytest.mark.parametrize("dtype,batch,hq,hkv,ctx,nodes,even", [
-    # bf16: 20 key tiles and 80 pairs of a key and a query tile per CU, 1250 tokens
+    # bf16: 20 key tiles and 80 pairs of a key and a query tile per CU, or 14 and 150; 1250 tokens
+    (0, 9, 32, 8, 2029, 86, True), (0, 9, 32, 8, 2029, 40, False), (0, 7, 32, 8, 1800, 110, False),
     (0, 1, 32, 8, 4096, 48, False), (0, 1, 32, 8, 32768, 48, True), (0, 8, 32, 8, 1000, 48, False),
     (0, 8, 32, 8, 4096, 48, True), (0, 4, 8, 2, 4096, 48, False), (0, 16, 8, 2, 8192, 48, True),
     (0, 8, 16, 8, 4096, 16, False), (0, 8, 16, 8, 8192, 48, True), (0, 47, 32, 8, 1200, 30, False),

@@ -86,6 +86,19 @@ def test_many_requests_and_shares_of_many_streams():
     check(wl.custom_layout(8, rows_for(rng, 8, 256, 1), ctx, hq=8, hkv=1, seed=9), reqs=range(0, 256, 17))
 
 
+def test_large_grid_of_the_four_wave_shape():
+    """100 requests of 1 to 8 query tiles that one split would fill the chip
+    with: shares of several streams, most of them whole, ragged contexts."""
+    rng = np.random.default_rng(6)
+    ctx = [1700] + [int(x) for x in rng.integers(1, 1700, 99)]
+    p = [[2, 5, 9, 13]] + rows_for(rng, 16, 99, 4)
+    p = [r if sum(16 - x for x in r) <= 48 else r[2:] for r in p]      # at most 64 nodes with the block
+    lay = wl.custom_layout(16, p, ctx, hq=32, hkv=8, seed=10)
+    lay_nodes = [16 + sum(16 - x for x in r) for r in p]
+    assert 33 <= max(lay_nodes) <= 64 and sum(-(-4 * n // 128) for n in lay_nodes) * 8 >= 768
+    check(lay, reqs=range(0, 100, 9))
+
+
 def test_page_list_longer_than_one_staging():
     """256 streams of 40,000 tokens: a workgroup's piece is longer than the
     32,768 tokens whose page ids it stages at a time. The logical pages share
