@@ -44,7 +44,9 @@ def percentiles(v) -> dict:
     a = np.asarray(v, np.float64)
     return {"median": round(float(np.median(a)), 4), "p10": round(float(np.percentile(a, 10)), 4),
             "p90": round(float(np.percentile(a, 90)), 4)}
-KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_04446_amd", "csrc", f) for f in ("attention.hip", "common.h")]
+# the files that the attention kernels are compiled from
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_04446_amd", "csrc", f)
+               for f in ("attention.hip", "attention_device.h", "balanced.hip", "common.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cascade_attention_traffic.json")
 
 
@@ -120,9 +122,10 @@ def kernel_sha() -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(config: int, kv_split: int, resolved_split: int):
+def measured_traffic(config: int, kv_split: int, resolved_split: int, kernel: str | None = None):
     """HBM bytes per launch from committed rocprofv3 counters, if they were taken
-    on the current kernel source and the same launch configuration."""
+    on the current kernel source, the same launch configuration and (if given)
+    the same kernel."""
     try:
         with open(TRAFFIC_FILE) as f:
             rec = json.load(f)
@@ -131,7 +134,7 @@ def measured_traffic(config: int, kv_split: int, resolved_split: int):
     key = f"config{config}"
     r = rec.get(key)
     if not r or r.get("kernel_sha") != kernel_sha() or r.get("kv_split") != kv_split \
-            or r.get("resolved_kv_split") != resolved_split:
+            or r.get("resolved_kv_split") != resolved_split or (kernel is not None and r.get("kernel") != kernel):
         return None
     return r.get("hbm_bytes_per_launch")
 
@@ -174,7 +177,7 @@ def trace_summary(d: str, warmup: int, steps: int) -> dict:
     paths = glob.glob(os.path.join(d, "**", "*kernel_trace.csv"), recursive=True)
     if not paths:
         raise FileNotFoundError(f"no kernel_trace.csv under {d}")
-    names = ["cascade_bf16_packed_kernel", "cascade_bf16_wide_kernel", "cascade_bf16_kernel",
+    names = ["cascade_balanced_kernel", "cascade_bf16_packed_kernel", "cascade_bf16_wide_kernel", "cascade_bf16_kernel",
              "cascade_attention_kernel", "split_merge_kernel"]
     per = {}
     for path in paths:
@@ -580,7 +583,9 @@ def main():
     tflops = flops / t_s / 1e12
     t_hbm = prefix_bytes / (HBM_PEAK_GBPS * 1e9)
     t_mfma = flops / (MFMA_PEAK_TFLOPS[spec.dtype] * 1e12)
-    traffic = measured_traffic(args.config, args.kv_split, kv_split) if args.tree == "canonical" else None
+    kernel = attention_kernel_name({"dtype": spec.dtype,
+                                    "config": {"row_group": row_group, "packed": packed, "balanced": balanced}})
+    traffic = measured_traffic(args.config, args.kv_split, kv_split, kernel) if args.tree == "canonical" else None
     parts = {"kernel_ms": round(kern_ms, 4), "merge_ms": round(merge_ms, 4), "splits": n_splits}
     if t_mfma > t_hbm:
         roof = {"bound": "mfma", "achieved": round(tflops, 2), "peak": MFMA_PEAK_TFLOPS[spec.dtype],

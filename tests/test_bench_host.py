@@ -4,6 +4,7 @@ readers, the HBM-traffic record and its use, and the one-GPU guard."""
 import csv
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -72,6 +73,31 @@ def test_record_and_use_traffic(tmp_path, monkeypatch):
     assert bench.measured_traffic(4, 0, 8192) is None
 
 
+def test_traffic_of_another_kernel_is_not_used(tmp_path, monkeypatch):
+    rec_file = tmp_path / "traffic.json"
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(rec_file))
+    rec_file.write_text(json.dumps({"config3": {"kernel_sha": bench.kernel_sha(), "kv_split": 0, "resolved_kv_split": 704,
+                                                "kernel": "cascade_bf16_kernel", "hbm_bytes_per_launch": 5}}))
+    assert bench.measured_traffic(3, 0, 704, "cascade_bf16_kernel") == 5
+    assert bench.measured_traffic(3, 0, 704, "cascade_balanced_kernel") is None
+
+
+def test_kernel_sources_are_all_hashed():
+    """Every file that an attention launcher is compiled from, its own headers
+    included, enters the hash that recorded counters are matched by."""
+    csrc = os.path.join(ROOT, "paper_2606_04446_amd", "csrc")
+    text = {f: open(os.path.join(csrc, f)).read() for f in os.listdir(csrc)}
+    todo = [f for f, t in text.items() if f.endswith(".hip") and "cascade_" in t and "__global__" in t]
+    assert {"attention.hip", "balanced.hip"} <= set(todo)
+    need = set()
+    while todo:
+        f = todo.pop()
+        if f not in need:
+            need.add(f)
+            todo += [h for h in re.findall(r'#include "([^"]+)"', text[f]) if h in text]
+    assert need <= {os.path.basename(p) for p in bench.KERNEL_SRCS}
+
+
 def test_record_traffic_adds_the_split_merge(tmp_path, monkeypatch):
     """With a split context the operation is the attention kernel plus the
     split merge that reads the partial states back: both kernels' counters."""
@@ -119,6 +145,8 @@ def test_attention_kernel_name_follows_the_shape():
     assert k({"dtype": "bf16", "config": {"row_group": 128}}) == "cascade_bf16_kernel"
     assert k({"dtype": "bf16", "config": {"row_group": 384, "packed": False}}) == "cascade_bf16_wide_kernel"
     assert k({"dtype": "bf16", "config": {"row_group": 384, "packed": True}}) == "cascade_bf16_packed_kernel"
+    for dtype in ("bf16", "f32"):
+        assert k({"dtype": dtype, "config": {"row_group": 128, "balanced": True}}) == "cascade_balanced_kernel"
 
 
 def test_kernel_names_match_whole_identifiers():
