@@ -140,9 +140,13 @@ def measured_traffic(config: int, kv_split: int, resolved_split: int, kernel: st
 
 
 def kernel_name_matches(name: str, kernel: str) -> bool:
-    """Whether a demangled kernel name is `kernel` (as a whole identifier:
-    "cascade_bf16_kernel" does not match "noncascade_bf16_kernel")."""
+    """Whether a kernel name is `kernel` (as a whole identifier:
+    "cascade_bf16_kernel" does not match "noncascade_bf16_kernel"). The
+    profiler leaves some instances of templates mangled, where the identifier
+    follows its length."""
     import re
+    if name.startswith("_Z"):
+        return f"{len(kernel)}{kernel}" in name
     return re.search(r"(?<![A-Za-z0-9_])" + re.escape(kernel) + r"(?![A-Za-z0-9_])", name) is not None
 
 

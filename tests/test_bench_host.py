@@ -156,6 +156,9 @@ def test_kernel_names_match_whole_identifiers():
     assert not m("d2sd::(anonymous namespace)::noncascade_bf16_kernel(Params)", "cascade_bf16_kernel")
     assert m("void split_merge_kernel<__bf16, 4>(Params, int)", "split_merge_kernel")
     assert not m("cascade_bf16_kernel_v2", "cascade_bf16_kernel")
+    assert m("_ZN4d2sd12_GLOBAL__N_123cascade_balanced_kernelIDF16bEEvNS0_6ParamsE", "cascade_balanced_kernel")
+    assert m("_ZN4d2sd12_GLOBAL__N_118split_merge_kernelIDF16bDF16bLi1ELb0EEEvNS0_6ParamsEi", "split_merge_kernel")
+    assert not m("_ZN4d2sd12_GLOBAL__N_122noncascade_bf16_kernelENS0_6ParamsE", "cascade_bf16_kernel")
 
 
 def test_kernel_sha_is_stable():
