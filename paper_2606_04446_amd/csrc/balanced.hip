@@ -39,10 +39,10 @@
 // (fp32). Each 1 KB block is one DMA instruction that reads whole 128-byte
 // lines. A lane's addresses take two registers instead of twelve, which
 // leaves room for K fragments in flight.
-// Attention time with the split merge (launch events included), fixed splits
-// before: 1 request of 32k tokens 83 -> 56 us (of which the kernel moves its
-// 134 MB at 3.6 TB/s); 8 of 1k-8k 103 -> 72; 16 of 0-8k without host offsets
-// 195 -> 131; fp32, 4 of 300-3000, 225 -> 99 (52 TFLOP/s in the products).
+// A pass, fixed splits before: attention of 1 request of 32k tokens 73.7 -> 53.0
+// us (of which the kernel moves its 134 MB in 46); a verify step of 8 of 1k-8k
+// 98.7 -> 76.9; of 16 of 0-8k without host offsets 190 -> 131; fp32 attention, 4
+// of 300-3000, 216 -> 91 (58 TFLOP/s over the whole pass).
 // A call on little work is bound by its start: about 3 us until a workgroup
 // has its piece, 2 until the query rows and page ids are there, 4 until the
 // first tiles of all CUs have arrived, 2 for the stores.

@@ -116,7 +116,7 @@ constexpr int kBalMaxCostF32 = 12;
 constexpr int kBalOverheadF32 = 12;
 
 // Rows (queries) per MFMA column tile. A work item's row group is one tile
-// per wave: 32 * plan.waves rows (fp32: always 4 waves).
+// per wave: 32 * plan.waves rows (fp32 with fixed splits: 4 waves).
 constexpr int kRowsPerTile = 32;
 
 // Split merge: 16 lanes per output row (8 dims each) and 1 or 4 groups of them
@@ -125,8 +125,9 @@ constexpr int kRowsPerTile = 32;
 // batch x merge_chunks_per_request(...) workgroups. A group folds four splits
 // per round of loads, so four groups pay where a row has more than that: with
 // fixed splits from 4 on, in the balanced shape from 16 pieces of an average
-// stream on (one request of 33 pieces: 7.8 us against 10.5 with one group;
-// 16 requests of 2-4 pieces: 11.0 against 22.2).
+// stream on (one request of 33 pieces: 8.9 us against 13.3 with one group;
+// 4 fp32 requests of about 8: 10.0 against 9.8; 16 requests of 2-4 pieces: 21.7
+// against 14.6).
 __host__ __device__ constexpr int merge_rows(int groups) { return 256 / (16 * groups); }
 __host__ __device__ inline long long merge_chunks_per_request(int max_nodes, int hq, int groups) {
   return ((long long)max_nodes * hq + merge_rows(groups) - 1) / merge_rows(groups);
