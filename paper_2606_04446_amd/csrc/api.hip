@@ -308,6 +308,11 @@ struct Shape {
 //    28; 16 of 4000: 974 -> 463; 64 of 500: 569 -> 311), but not where the fixed
 //    plan is one unsplit round that fills the CUs with a short context (16 of 66:
 //    43 -> 54, of 100: 49 -> 59, of 200: 69 -> 71; 64/8 heads, 4 of 66: 35 -> 39).
+// max_ctx_len is all that the host knows of the contexts. Where it is far above
+// them (8k-131k for contexts of 0.1-8k, as under capture) the even division still
+// takes 0.83 of the fixed splits' time in bf16 (63 batches of 1-64 requests, mean)
+// and 0.3 in fp32, but more where little is left to divide (1-2 requests of
+// 100-500 tokens: 17 -> 22-26; 64 of them: 52 -> 66).
 bool balanced_pays(const d2sd_attn_args* a, int G, const Shape& fixed, bool large_grid, long long g4) {
   if (a->stage == D2SD_STAGE_TREE || a->total_nodes == 0) return false;
   const long long ctx = a->max_ctx_len;

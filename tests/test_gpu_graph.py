@@ -54,6 +54,7 @@ def test_graph_replays_match_eager(cfg):
     args = m.attn_args(x["q"], x["k_cache"], x["v_cache"], case.d_pt, case.d_ctx, x["k_tree"], x["v_tree"],
                        case.d_ip, tree["anc_mask"], out, lse, total_nodes=total, max_nodes=case.max_nodes,
                        max_ctx_len=max_ctx, **kw)
+    assert m.cascade_division(args)[0] == (cfg == 3)
     ws = torch.empty(max(m.cascade_workspace_size(args), 1), dtype=torch.uint8, device=dev)
     acc = m.accept_path(B, case.d_ip, total, tree["parent"], tree["depth"], tree["path_id"], d_draft, d_argmax)
 
